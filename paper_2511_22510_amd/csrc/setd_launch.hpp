@@ -73,13 +73,16 @@ inline bool multi2d_ok(const Geo& g, bool lean, int nl)
 inline int multi2d_slot(int n) { return n == 64 ? 0 : n == 128 ? 1 : n == 256 ? 2 : 3; }
 template <typename T>
 hipError_t launch_multi2d(const MultiClass (&cls)[4], int pass, int sub, hipStream_t s);
-// 1D lattices: nsteps steps per launch// 1D lattices: nsteps steps per launch (MODE_STEP) or the initial condition (MODE_IC)
+// 1D lattices: nsteps steps per launch (MODE_STEP) or the initial condition (MODE_IC)
 template <typename T>
 hipError_t launch_line1d(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps, int nl,
                          hipStream_t s);
 // box-averaged width: class sums of one realization, then sum_c |A_c|^2 per level
 template <typename T>
 hipError_t launch_boxwidth(const BoxArgs& a, size_t ncls, hipStream_t s);
+// 1D lattices: the level sums of every realization in one launch
+template <typename T>
+hipError_t launch_boxline(const BoxLineArgs& a, hipStream_t s);
 
 // (tile width, columns per thread) of axis-pass variant `var` for line length n
 void axis_shape(int precision, int n, int var, int* tile, int* lpt);

@@ -1033,30 +1033,43 @@ setd_status Plan::observe(int kind, double* out, size_t cap, size_t* len)
         int J = 0;
         while ((1 << J) < N) J++;
         if (cap < (size_t)J) return fail(SETD_E_INVAL, "output needs %d doubles", J);
-        BoxArgs ba{};
-        ba.g = g;
-        ba.items = items_dev;
-        ba.total = (int)S;
-        ba.N = N;
-        ba.J = J;
-        ba.cls = reinterpret_cast<double*>(ws + lay.boxcls);
-        ba.sums = acc;
-        // whole coarse levels, from l = N down, while they fit the LDS table
-        size_t tail = 0;
-        for (int j = J; j >= 1; j--) {
-            size_t c = 1;
-            for (int i = 0; i < d.ndim; i++) c *= (size_t)(N >> j);
-            if (tail + c > 1024) break;
-            tail += c;
-        }
-        ba.lds_base = lay.boxn - tail;
-        ba.nlds = (int)tail;
         SETD_HIP(launch_fill64(acc, J + 1, 0.0, stream));
-        for (int r = 0; r < R; r++) {
-            ba.r = r;
-            SETD_HIP(launch_fill64(ba.cls, (int64_t)(2 * lay.boxn), 0.0, stream));
-            if (d.precision == 32) SETD_HIP((launch_boxwidth<float>(ba, lay.boxn, stream)));
-            else SETD_HIP((launch_boxwidth<double>(ba, lay.boxn, stream)));
+        if (d.ndim == 1) {
+            BoxLineArgs bl{};
+            bl.g = g;
+            bl.items = items_dev;
+            bl.nitems = R;
+            bl.N = N;
+            bl.J = J;
+            bl.tw = reinterpret_cast<const double*>(ws + lay.tw64[0]);
+            bl.sums = acc;
+            if (d.precision == 32) SETD_HIP((launch_boxline<float>(bl, stream)));
+            else SETD_HIP((launch_boxline<double>(bl, stream)));
+        } else {
+            BoxArgs ba{};
+            ba.g = g;
+            ba.items = items_dev;
+            ba.total = (int)S;
+            ba.N = N;
+            ba.J = J;
+            ba.cls = reinterpret_cast<double*>(ws + lay.boxcls);
+            ba.sums = acc;
+            // whole coarse levels, from l = N down, while they fit the LDS table
+            size_t tail = 0;
+            for (int j = J; j >= 1; j--) {
+                size_t c = 1;
+                for (int i = 0; i < d.ndim; i++) c *= (size_t)(N >> j);
+                if (tail + c > 1024) break;
+                tail += c;
+            }
+            ba.lds_base = lay.boxn - tail;
+            ba.nlds = (int)tail;
+            for (int r = 0; r < R; r++) {
+                ba.r = r;
+                SETD_HIP(launch_fill64(ba.cls, (int64_t)(2 * lay.boxn), 0.0, stream));
+                if (d.precision == 32) SETD_HIP((launch_boxwidth<float>(ba, lay.boxn, stream)));
+                else SETD_HIP((launch_boxwidth<double>(ba, lay.boxn, stream)));
+            }
         }
         double sums[16];
         SETD_HIP(hipMemcpyAsync(sums, acc, (size_t)(J + 1) * sizeof(double), hipMemcpyDeviceToHost, stream));

@@ -123,6 +123,16 @@ struct BoxArgs {
     int nlds;         // classes summed in LDS, at most 1024
 };
 
+// arguments of the box-averaged width of 1D lattices: every realization in one launch
+struct BoxLineArgs {
+    Geo g;
+    const Item* items;
+    int nitems;
+    int N, J;           // sites of a line, log2 N
+    const double* tw;   // exp(-2 pi i k / N) in FP64, interleaved
+    double* sums;       // [J + 1]: sums[0] sum_a |h_a|^2, sums[j] sum_c |A_c|^2 of box size 2^j (a != 0)
+};
+
 // observable reductions
 enum { RED_SK = 0, RED_WIDTH = 1, RED_TWOTIME = 2, RED_RESPONSE = 3 };
 
