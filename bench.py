@@ -232,6 +232,9 @@ def pass_roofline(r, p, names, traffic_workload=None):
     gap = 0.0 if two_streams else max(0.0, (float(ev_avg.sum()) - steps_ev) / npass)
     avg = ev_avg - gap
     model = survey_pass_bytes(p)
+    if npass == 2 and len(model) == 4:
+        # the 3D step in two passes: the axis-1 passes of the model ride with the rows
+        model = [model[0] + model[1] + model[2], model[3]]
     moved = [float(info.pass_bytes[i]) for i in range(npass)]
     dom = int(np.argmax(avg))
     passes = [{"kernel": names[i], "avg_us": float(avg[i] * 1e6), "avg_us_events": float(ev_avg[i] * 1e6),
@@ -270,6 +273,8 @@ def pass_names_2d(info, N):
 
 
 def pass_names_3d(info, N):
+    if int(info.passes_per_step) == 2:
+        return ["k_rows32<%d>" % N, "k_ax01<%d>" % N]
     return ["k_axis1<inverse,%d>" % N, "k_row_cplx<%d>" % N, "k_axis1<forward,%d>" % N, axis0_name(info, N)]
 
 

@@ -202,7 +202,8 @@ typedef struct {
     size_t spectral_len;      /* complex values per realization crossing the ABI   */
     size_t kept_modes;        /* stored (non-dealiased) modes per realization      */
     int nbins;                /* shell bins of the S(k) and two-time observables   */
-    int passes_per_step;      /* kernel launches per time step                     */
+    int passes_per_step;      /* kernel launches per time step (a 3D plan whose
+                                 step takes two passes says so once bound)         */
     double alg_bytes_per_step;/* HBM bytes one step must move (all realizations)   */
     double site_updates_per_step; /* prod n[i] * realizations                      */
     double pass_bytes[4];     /* HBM bytes each kernel launch of a step must move,

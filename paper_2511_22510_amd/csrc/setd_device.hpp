@@ -349,12 +349,26 @@ constexpr int slot_step(int d) { return PAD > 0 ? d + (d >> PAD) : d; }
 // + r NS cross a multiple of 2^PAD exactly where r NS does when NS R >= 2^PAD
 // (offset slot_step(r NS)) and never otherwise (offset r NS); the reads
 // t + q N/8 with t < N/8 likewise sit at slot(t) + slot_step(q N/8).
-template <typename T, int N, int R, int NS, int PAD, int NL>
+// WAVE: the N/8 threads of a line lie in one wavefront.  Its LDS operations
+// complete in order, so the exchange orders the compiler's accesses only and
+// wavefronts do not wait for each other.
+template <bool WAVE>
+__device__ __forceinline__ void exchange_sync()
+{
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+template <typename T, int N, int R, int NS, int PAD, int NL, bool WAVE = false>
 __device__ __forceinline__ void fft_exchange(cx<T> (&v)[NL][8], int t, cx<T>* lds, int stride, int lstep)
 {
     constexpr int NB = 8 / R;
     constexpr bool LIN = PAD == 0 || NS * R >= (1 << PAD);
-    __syncthreads();
+    exchange_sync<WAVE>();
 #pragma unroll
     for (int b = 0; b < NB; b++) {
         const int j = t + b * (N / 8);
@@ -366,7 +380,7 @@ __device__ __forceinline__ void fft_exchange(cx<T> (&v)[NL][8], int t, cx<T>* ld
             for (int r = 0; r < R; r++) p[k * lstep + (LIN ? slot_step<PAD>(r * NS) : r * NS) * stride] = v[k][b + NB * r];
         }
     }
-    __syncthreads();
+    exchange_sync<WAVE>();
     const cx<T>* p = lds + lds_slot<PAD>(t) * stride;
 #pragma unroll
     for (int k = 0; k < NL; k++) {
@@ -377,27 +391,28 @@ __device__ __forceinline__ void fft_exchange(cx<T> (&v)[NL][8], int t, cx<T>* ld
 
 // NL independent line transforms X_k = sum_m x_m exp(SIGN 2 pi i k m / N),
 // unscaled, held by the same threads (same t, same twiddles).  Every thread of
-// the block must call it (it contains block barriers).
-template <typename T, int N, int SIGN, int PAD, int NL, typename TW>
+// the block must call it (it contains block barriers), except with WAVE.
+template <typename T, int N, int SIGN, int PAD, int NL, bool WAVE = false, typename TW>
 __device__ __forceinline__ void fft_lines(cx<T> (&v)[NL][8], int t, cx<T>* lds, int stride, int lstep, const TW& tw)
 {
+    static_assert(!WAVE || N <= 512, "a line of one wavefront");
     static_assert(N >= 8 && (N & (N - 1)) == 0, "power-of-two line length >= 8");
     constexpr int R0 = FftPlan<N>::R0;
     constexpr int NST = FftPlan<N>::NST;
 #pragma unroll
     for (int k = 0; k < NL; k++) fft_stage0<T, N, R0, SIGN>(v[k]);
     if constexpr (NST > 1) {
-        fft_exchange<T, N, R0, 1, PAD, NL>(v, t, lds, stride, lstep);
+        fft_exchange<T, N, R0, 1, PAD, NL, WAVE>(v, t, lds, stride, lstep);
 #pragma unroll
         for (int k = 0; k < NL; k++) tw_stage<T, N, SIGN>(v[k], tw, 0);
     }
     if constexpr (NST > 2) {
-        fft_exchange<T, N, 8, R0, PAD, NL>(v, t, lds, stride, lstep);
+        fft_exchange<T, N, 8, R0, PAD, NL, WAVE>(v, t, lds, stride, lstep);
 #pragma unroll
         for (int k = 0; k < NL; k++) tw_stage<T, N, SIGN>(v[k], tw, 1);
     }
     if constexpr (NST > 3) {
-        fft_exchange<T, N, 8, R0 * 8, PAD, NL>(v, t, lds, stride, lstep);
+        fft_exchange<T, N, 8, R0 * 8, PAD, NL, WAVE>(v, t, lds, stride, lstep);
 #pragma unroll
         for (int k = 0; k < NL; k++) tw_stage<T, N, SIGN>(v[k], tw, 2);
     }

@@ -73,6 +73,20 @@ inline bool multi2d_ok(const Geo& g, bool lean, int nl)
 inline int multi2d_slot(int n) { return n == 64 ? 0 : n == 128 ? 1 : n == 256 ? 2 : 3; }
 template <typename T>
 hipError_t launch_multi2d(const MultiClass (&cls)[4], int pass, int sub, hipStream_t s);
+// 3D complex fields whose step runs in two passes with the axis-1 transform
+// split between them (setd_part3.hip): complex64, 2/3 rule, SETD2 carry, CGL,
+// 32 to 256 points per axis (so the last axis of at most 256 points has its
+// 32 rows in LDS and the lines of a column tile fit the registers)
+inline bool part3_ok(const Geo& g, bool lean, int nl)
+{
+    if (g.ndim != 3 || !g.cplx || g.prec != 32 || g.dealias != 1 || g.rsn || !lean || nl != NL_CGL) return false;
+    for (int i = 0; i < 3; i++)
+        if (g.n[i] < 32 || g.n[i] > 256) return false;
+    return true;
+}
+// mode MODE_STEP, MODE_SYNC (phi -> line buffer) or MODE_RECOVER (line buffer -> phi)
+hipError_t launch_part3_axis0(const Geo& g, const Item* items, int nitems, int mode, int sub, hipStream_t s);
+hipError_t launch_part3_rows(const Geo& g, const Item* items, int nitems, int sub, hipStream_t s);
 // 1D lattices: nsteps steps per launch (MODE_STEP) or the initial condition (MODE_IC)
 template <typename T>
 hipError_t launch_line1d(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps, int nl,

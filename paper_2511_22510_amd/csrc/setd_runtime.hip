@@ -195,6 +195,7 @@ setd_status Plan::init(const setd_desc& desc)
     // used in, so those plans keep phi and F_{n-1})
     lean = d.ndim >= 2 && d.order == 2 && !d.history_readback && d.nl != NL_NONE && !d.noise_space &&
            axis0_register_ok(g, elt / 2);
+    part3 = part3_ok(g, lean, d.nl);
 
     // workspace layout, every buffer 256-byte aligned
     size_t off = 0;
@@ -253,7 +254,7 @@ setd_status Plan::init(const setd_desc& desc)
 int Plan::passes_per_step() const
 {
     if (d.nl == NL_NONE || d.ndim == 1) return 1;
-    return d.ndim == 2 ? 2 : 4;
+    return d.ndim == 2 || part3 ? 2 : 4;
 }
 
 // HBM bytes each pass must move with the stored (2/3-pruned) arrays: one read
@@ -294,6 +295,11 @@ void Plan::pass_bytes(double* out) const
     }
     const double small = (double)g.n[0] * g.kept[1] * kl;
     const double bigv = (double)g.n[0] * g.n[1] * kl;
+    if (part3) {
+        out[0] = 2.0 * bigv * e;                                // rows with the inner factor of axis 1
+        out[1] = (2.0 * bigv + (2.0 + hist) * st) * e;          // axis 0 with the outer factor
+        return;
+    }
     if (ps_grid()) {
         // phase shifts: pre and preb, four grids of the line buffer
         out[0] = (2.0 * small + 4.0 * bigv) * e;
@@ -343,6 +349,11 @@ static setd_status launch_pass_t(const Plan& p, int i, const Item* items_dev, in
         else SETD_HIP((launch_axis0<T>(g, items_dev, nitems, MODE_STEP, sub, p.tune.ax0, p.d.nl == NL_KPZ, p.lean, s)));
         return SETD_OK;
     }
+    if (p.part3) {
+        if (i == 0) SETD_HIP(launch_part3_rows(g, items_dev, nitems, sub, s));
+        else SETD_HIP(launch_part3_axis0(g, items_dev, nitems, MODE_STEP, sub, s));
+        return SETD_OK;
+    }
     // phase shifts: the axis-1 passes carry pre and preb to and from four grids
     const int ps = g.dealias == 2 ? 3 : 1;
     switch (i) {
@@ -390,6 +401,7 @@ static setd_status launch_ic_t(const Plan& p, const Item* items_dev, int nitems,
     SETD_HIP((launch_row<T>(g, items_dev, nitems, MODE_IC, 0, p.tune.row, 0, s)));
     if (g.ndim == 3) SETD_HIP((launch_axis1<T>(g, items_dev, nitems, -1, 0, p.tune.ax1, s)));
     SETD_HIP((launch_axis0<T>(g, items_dev, nitems, MODE_IC, 0, p.tune.ax0, p.d.nl == NL_KPZ, 0, s)));
+    if (p.part3) SETD_HIP(launch_part3_axis0(g, items_dev, nitems, MODE_SYNC, 0, s));
     return SETD_OK;
 }
 
@@ -397,6 +409,10 @@ template <typename T>
 static setd_status launch_sync_t(const Plan& p, const Item* items_dev, int nitems, hipStream_t s)
 {
     if (p.g.ndim == 1) return SETD_OK;   // a line keeps no partial transform
+    if (p.part3) {
+        SETD_HIP(launch_part3_axis0(p.g, items_dev, nitems, MODE_SYNC, 0, s));
+        return SETD_OK;
+    }
     SETD_HIP((launch_axis0<T>(p.g, items_dev, nitems, MODE_SYNC, 0, p.tune.ax0, p.d.nl == NL_KPZ, 0, s)));
     return SETD_OK;
 }
@@ -404,6 +420,10 @@ static setd_status launch_sync_t(const Plan& p, const Item* items_dev, int nitem
 template <typename T>
 static setd_status launch_recover_t(const Plan& p, const Item* items_dev, int nitems, hipStream_t s)
 {
+    if (p.part3) {
+        SETD_HIP(launch_part3_axis0(p.g, items_dev, nitems, MODE_RECOVER, 0, s));
+        return SETD_OK;
+    }
     SETD_HIP((launch_axis0<T>(p.g, items_dev, nitems, MODE_RECOVER, 0, p.tune.ax0, p.d.nl == NL_KPZ, 0, s)));
     return SETD_OK;
 }
@@ -653,7 +673,7 @@ setd_status Plan::autotune()
     Knob knobs[3] = {{&tune.row, 0, d.complex_field ? 4 : 16, row_pass, -1},
                      {&tune.ax0, lean ? 4 : 0, ax0_top, ax0_pass, -1},
                      {&tune.ax1, 0, 4, 0, 2}};
-    const int nknobs = (d.ndim == 3) ? 3 : 2;
+    const int nknobs = part3 ? 0 : ((d.ndim == 3) ? 3 : 2);   // the two-pass 3D step has no variants
     setd_status st = SETD_OK;
     for (int k = 0; k < nknobs && st == SETD_OK; k++) {
         Knob& kb = knobs[k];
@@ -1342,7 +1362,8 @@ setd_status setd_plan_info(const setd_plan* plan, setd_plan_info_t* info)
     info->spectral_len = p.nspec;
     info->kept_modes = p.kept_modes;
     info->nbins = p.nbins;
-    info->passes_per_step = p.passes_per_step();
+    // an unbound plan gives the passes of the general path
+    info->passes_per_step = (p.part3 && !p.bound) ? 4 : p.passes_per_step();
     info->alg_bytes_per_step = p.alg_bytes_per_step();
     info->site_updates_per_step = (double)p.nreal * p.R;
     p.pass_bytes(info->pass_bytes);

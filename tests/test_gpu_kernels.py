@@ -39,3 +39,50 @@ def test_line_box_widths(n, kind, prec, R, dealias):
     assert len(a) == len(b) == n.bit_length() - 1
     assert float(np.max(np.abs(a - b) / b)) <= (1e-10 if prec == 64 else 2e-4)
     g.close()
+
+
+def _trajectory_error(g, o, R, steps):
+    worst = 0.0
+    for n in steps:
+        g.step(n)
+        o.step(n)
+        for r in range(R):
+            a, b = g.get(r), o.get(r)
+            worst = max(worst, float(np.linalg.norm(a - b) / np.linalg.norm(b)))
+    return worst
+
+
+@pytest.mark.parametrize("n,R", [((32, 32, 32), 3), ((64, 32, 64), 2), ((32, 64, 128), 1), ((128, 128, 32), 1),
+                                 ((32, 256, 64), 1), ((256, 32, 128), 1), ((64, 128, 256), 1)])
+def test_two_pass_3d_step(n, R):
+    """The 3D complex step with the axis-1 transform split between two passes,
+    every axis length of its rule (1 to 8 x 32 along axis 1) and unequal axes:
+    steps, the recovered state, a set state (restarted history) and a set step
+    index follow the oracle to the FP32 bar of the workloads."""
+    S = _setd()
+    p = W.cgl(list(n), realizations=R, seed=11, ic_sigma=0.2)
+    g, o = S.Plan(p), O.Sim(p)
+    assert int(g.info.passes_per_step) == 2
+    assert float(np.linalg.norm(g.get(0) - o.get(0)) / np.linalg.norm(o.get(0))) <= 2e-4
+    assert _trajectory_error(g, o, R, (1, 2, 5)) <= 2e-4
+    x = W.random_spectrum(p, 5, scale=float(np.sqrt(np.prod(n))))
+    g.set(R - 1, x)
+    o.set(R - 1, x)
+    g.set_step(40)
+    o.set_step(40)
+    assert _trajectory_error(g, o, R, (1, 3)) <= 2e-4
+    g.close()
+
+
+@pytest.mark.parametrize("n,kw", [((16, 32, 32), {}), ((32, 32, 512), {}), ((32, 32, 32), dict(precision=64)),
+                                  ((32, 32, 32), dict(history_readback=1)), ((32, 32, 32), dict(order=1)),
+                                  ((32, 32, 32), dict(dealias=0)), ((32, 32, 32), dict(noise_space=1))])
+def test_general_3d_step_beside_the_rule(n, kw):
+    """3D complex plans that the two-pass rule does not take keep the four
+    passes and follow the oracle."""
+    S = _setd()
+    p = W.cgl(list(n), seed=12, ic_sigma=0.2, **kw)
+    g, o = S.Plan(p), O.Sim(p)
+    assert int(g.info.passes_per_step) == 4
+    assert _trajectory_error(g, o, 1, (1, 3)) <= (1e-10 if p["precision"] == 64 else 2e-4)
+    g.close()
