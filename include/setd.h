@@ -202,8 +202,9 @@ typedef struct {
     size_t spectral_len;      /* complex values per realization crossing the ABI   */
     size_t kept_modes;        /* stored (non-dealiased) modes per realization      */
     int nbins;                /* shell bins of the S(k) and two-time observables   */
-    int passes_per_step;      /* kernel launches per time step (a 3D plan whose
-                                 step takes two passes says so once bound)         */
+    int passes_per_step;      /* kernel launches per time step (a plan whose
+                                 step takes fewer passes than the general 2D or
+                                 3D path says so once bound)                      */
     double alg_bytes_per_step;/* HBM bytes one step must move (all realizations)   */
     double site_updates_per_step; /* prod n[i] * realizations                      */
     double pass_bytes[4];     /* HBM bytes each kernel launch of a step must move,
@@ -353,7 +354,7 @@ setd_status setd_job_times(setd_server* server, setd_job job, double* out4);
 /* Counters of the server since its creation: out[0] scheduler ticks that ran
    steps, out[1] pass launches those ticks queued (per launch unit and
    sub-step), out[2] the launches among them that several lattice classes
-   shared (2D real fields of square lattices N = 64..512, complex64, 2/3 rule,
+   shared (2D real fields of square lattices N = 128..512, complex64, 2/3 rule,
    SETD2, phi^3 nonlinearities: one launch per pass for all of them;
    environment SETD_SERVER_MULTI=0 at creation keeps one launch per class).
    cap >= 3; *len receives 3. */

@@ -1493,20 +1493,20 @@ k_axis0r(AxisArgs a)
 
 // ---------------------------------------------------------------- launches shared by lattice classes
 // The 2D real-field classes of a serving tick that differ only in the lattice
-// size (square N = 64, 128, 256 or 512; complex64; 2/3 rule; SETD2 carry;
+// size (square N = 128, 256 or 512; complex64; 2/3 rule; SETD2 carry;
 // the phi^3 nonlinearities) advance in one launch per pass.  The arguments
 // hold one slot per size; a block finds its slot from the slots' first blocks
 // and runs that size's body, so every slot's body is compiled once and its
 // arguments are read at fixed offsets.  Row pass: 256-thread blocks at every
 // size (the same LDS, 18 KiB).  Axis-0 pass: 512-thread blocks; tile 8 for
-// N = 512 and 16 otherwise, and for N <= 128 a block holds SUB = 2 or 4
+// N = 512 and 16 otherwise, and for N = 128 a block holds SUB = 2
 // sub-blocks of one item (sub-block k runs tile SUB b + k of the item's
 // b-th block; those past its last tile read and store nothing), so that all
 // threads of a block meet the same barriers; every size uses 36 KiB of LDS.
-constexpr int MULTI_SLOTS = 4;   // N = 64 << slot
+constexpr int MULTI_SLOTS = 3;   // N = 128 << slot
 
-__host__ __device__ constexpr int multi_tile(int slot) { return slot == 3 ? 8 : 16; }
-__host__ __device__ constexpr int multi_sub(int slot) { return 512 / (multi_tile(slot) * ((64 << slot) / 8)); }
+__host__ __device__ constexpr int multi_tile(int slot) { return slot == 2 ? 8 : 16; }
+__host__ __device__ constexpr int multi_sub(int slot) { return 512 / (multi_tile(slot) * ((128 << slot) / 8)); }
 
 struct MultiRowArgs {
     RowArgs a[MULTI_SLOTS];
@@ -1534,7 +1534,7 @@ __device__ __forceinline__ int multi_slot(const int (&first)[MULTI_SLOTS + 1], i
 template <typename T, int SLOT>
 __device__ __forceinline__ void row_multi_slot(const MultiRowArgs& m, int b)
 {
-    constexpr int N = 64 << SLOT;
+    constexpr int N = 128 << SLOT;
     const int local = b - m.first[SLOT];
     row_real_body<T, N, 3, 0, true, false>(m.a[SLOT], local % m.gx[SLOT], local / m.gx[SLOT], threadIdx.x);
 }
@@ -1546,15 +1546,14 @@ __global__ void __launch_bounds__(256) k_row_multi(MultiRowArgs m)
     switch (multi_slot(m.first, b)) {
     case 0: row_multi_slot<T, 0>(m, b); break;
     case 1: row_multi_slot<T, 1>(m, b); break;
-    case 2: row_multi_slot<T, 2>(m, b); break;
-    default: row_multi_slot<T, 3>(m, b); break;
+    default: row_multi_slot<T, 2>(m, b); break;
     }
 }
 
 template <typename T, int SLOT>
 __device__ __forceinline__ void axis0_multi_slot(const MultiAxArgs& m, int lg)
 {
-    constexpr int N0 = 64 << SLOT, TILE = multi_tile(SLOT), SUB = multi_sub(SLOT);
+    constexpr int N0 = 128 << SLOT, TILE = multi_tile(SLOT), SUB = multi_sub(SLOT);
     constexpr int SUBT = TILE * N0 / 8;   // threads of a sub-block
     constexpr int PAD = 3;
     constexpr unsigned SUBLDS = (unsigned)(TILE * lds_len<N0, PAD>() * 2 * sizeof(T));
@@ -1565,7 +1564,7 @@ __device__ __forceinline__ void axis0_multi_slot(const MultiAxArgs& m, int lg)
                                            (unsigned)k * SUBLDS, blk == 0);
 }
 
-// (the four bodies in one function need more registers than any of them
+// (the three bodies in one function need more registers than any of them
 // alone: at the three waves per SIMD targeted here they fit without spills)
 template <typename T>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3)))
@@ -1575,8 +1574,7 @@ k_axis0_multi(MultiAxArgs m)
     switch (multi_slot(m.first, lg)) {
     case 0: axis0_multi_slot<T, 0>(m, lg); break;
     case 1: axis0_multi_slot<T, 1>(m, lg); break;
-    case 2: axis0_multi_slot<T, 2>(m, lg); break;
-    default: axis0_multi_slot<T, 3>(m, lg); break;
+    default: axis0_multi_slot<T, 2>(m, lg); break;
     }
 }
 

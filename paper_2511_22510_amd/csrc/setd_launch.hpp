@@ -55,9 +55,9 @@ hipError_t launch_fdt_reduce(const Geo& g, const double* dacc, int total, int M,
 template <typename T>
 hipError_t launch_rsn(const Geo& g, const Item* items, int nitems, int sub, int var1, int var0, hipStream_t s);
 // Lattice classes that share one launch per pass (k_row_multi, k_axis0_multi):
-// 2D real fields on square lattices of N = 64, 128, 256 or 512 points, complex64,
+// 2D real fields on square lattices of N = 128, 256 or 512 points, complex64,
 // 2/3 rule, SETD2 with the carry storage, a phi^3 nonlinearity, Fourier-space
-// noise.  Slot s of launch_multi2d takes the class of N = 64 << s (nitems 0:
+// noise.  Slot s of launch_multi2d takes the class of N = 128 << s (nitems 0:
 // none); pass 0 is the row pass, 1 the axis-0 pass with the update.
 struct MultiClass {
     Geo g;
@@ -68,11 +68,11 @@ inline bool multi2d_ok(const Geo& g, bool lean, int nl)
 {
     const int n = g.n[0];
     return g.ndim == 2 && !g.cplx && g.prec == 32 && g.dealias == 1 && !g.rsn && lean && n == g.n[1] &&
-           (n == 64 || n == 128 || n == 256 || n == 512) && (nl == NL_PHI3 || nl == NL_PHI3_CONS);
+           (n == 128 || n == 256 || n == 512) && (nl == NL_PHI3 || nl == NL_PHI3_CONS);
 }
-inline int multi2d_slot(int n) { return n == 64 ? 0 : n == 128 ? 1 : n == 256 ? 2 : 3; }
+inline int multi2d_slot(int n) { return n == 128 ? 0 : n == 256 ? 1 : 2; }
 template <typename T>
-hipError_t launch_multi2d(const MultiClass (&cls)[4], int pass, int sub, hipStream_t s);
+hipError_t launch_multi2d(const MultiClass (&cls)[3], int pass, int sub, hipStream_t s);
 // 3D complex fields whose step runs in two passes with the axis-1 transform
 // split between them (setd_part3.hip): complex64, 2/3 rule, SETD2 carry, CGL,
 // 32 to 256 points per axis (so the last axis of at most 256 points has its
@@ -87,6 +87,18 @@ inline bool part3_ok(const Geo& g, bool lean, int nl)
 // mode MODE_STEP, MODE_SYNC (phi -> line buffer) or MODE_RECOVER (line buffer -> phi)
 hipError_t launch_part3_axis0(const Geo& g, const Item* items, int nitems, int mode, int sub, hipStream_t s);
 hipError_t launch_part3_rows(const Geo& g, const Item* items, int nitems, int sub, hipStream_t s);
+// 2D real fields of 32 or 64 points per axis under the 2/3 rule: nsteps whole
+// steps in one launch, a workgroup per realization (setd_small_impl.hpp).  At
+// 128 points one CU takes longer for a step (about 14 us of VALU issue) than
+// the two passes over the whole GPU do.
+inline bool small2d_ok(const Geo& g, int nl)
+{
+    if (g.ndim != 2 || g.cplx || g.dealias != 1 || g.rsn || nl == NL_NONE) return false;
+    return (g.n[0] == 32 || g.n[0] == 64) && (g.n[1] == 32 || g.n[1] == 64);
+}
+template <typename T>
+hipError_t launch_small2d(const Geo& g, const Item* items, int nitems, int sub, int nsteps, int nl, bool lean,
+                          hipStream_t s);
 // 1D lattices: nsteps steps per launch (MODE_STEP) or the initial condition (MODE_IC)
 template <typename T>
 hipError_t launch_line1d(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps, int nl,

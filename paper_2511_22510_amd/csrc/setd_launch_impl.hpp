@@ -376,14 +376,14 @@ hipError_t launch_rsn(const Geo& g, const Item* items, int nitems, int sub, int 
 }
 
 template <typename T>
-hipError_t launch_multi2d(const MultiClass (&cls)[4], int pass, int sub, hipStream_t s)
+hipError_t launch_multi2d(const MultiClass (&cls)[3], int pass, int sub, hipStream_t s)
 {
-    static_assert(MULTI_SLOTS == 4, "one class slot per lattice size 64..512");
+    static_assert(MULTI_SLOTS == 3, "one class slot per lattice size 128..512");
     int total = 0;
     if (pass == 0) {
         MultiRowArgs m{};
         for (int k = 0; k < MULTI_SLOTS; k++) {
-            const int N = 64 << k, lpw = 256 / (N / 8);
+            const int N = 128 << k, lpw = 256 / (N / 8);
             m.first[k] = total;
             RowArgs& a = m.a[k];
             a.g = cls[k].g;

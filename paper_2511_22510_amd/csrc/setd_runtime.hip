@@ -196,6 +196,7 @@ setd_status Plan::init(const setd_desc& desc)
     lean = d.ndim >= 2 && d.order == 2 && !d.history_readback && d.nl != NL_NONE && !d.noise_space &&
            axis0_register_ok(g, elt / 2);
     part3 = part3_ok(g, lean, d.nl);
+    small = small2d_ok(g, d.nl);
 
     // workspace layout, every buffer 256-byte aligned
     size_t off = 0;
@@ -253,7 +254,7 @@ setd_status Plan::init(const setd_desc& desc)
 
 int Plan::passes_per_step() const
 {
-    if (d.nl == NL_NONE || d.ndim == 1) return 1;
+    if (d.nl == NL_NONE || d.ndim == 1 || small) return 1;
     return d.ndim == 2 || part3 ? 2 : 4;
 }
 
@@ -267,8 +268,8 @@ void Plan::pass_bytes(double* out) const
     const double kl = (double)g.kept[g.ndim - 1];
     const double st = (double)kept_modes;                 // stored modes
     const double hist = (d.order == 2 && !lean) ? 2.0 : 0.0;   // read + write F_{n-1} (lean: one carry array)
-    if (d.ndim == 1) {
-        // a line: state (and F_{n-1}) in and out once per launch, given per step
+    if (d.ndim == 1 || small) {
+        // a line or small lattice: state (and F_{n-1}) in and out once per launch, given per step
         // of a one-step launch
         out[0] = (2.0 + hist) * st * e;
         return;
@@ -367,6 +368,7 @@ static setd_status launch_pass_t(const Plan& p, int i, const Item* items_dev, in
 
 setd_status Plan::launch_pass(int i, const Item* items_dev, int nitems, int sub, hipStream_t s) const
 {
+    if (small) return launch_steps(items_dev, nitems, sub, 1, s);
     return d.precision == 32 ? launch_pass_t<float>(*this, i, items_dev, nitems, sub, s)
                              : launch_pass_t<double>(*this, i, items_dev, nitems, sub, s);
 }
@@ -376,6 +378,13 @@ setd_status Plan::launch_noise(const Item* items_dev, int nitems, int sub, hipSt
     if (!rsn_grid()) return SETD_OK;
     if (d.precision == 32) SETD_HIP((launch_rsn<float>(g, items_dev, nitems, sub, tune.ax1, tune.ax0, s)));
     else SETD_HIP((launch_rsn<double>(g, items_dev, nitems, sub, tune.ax1, tune.ax0, s)));
+    return SETD_OK;
+}
+
+setd_status Plan::launch_steps(const Item* items_dev, int nitems, int sub, int n, hipStream_t s) const
+{
+    if (d.precision == 32) SETD_HIP((launch_small2d<float>(g, items_dev, nitems, sub, n, d.nl, lean, s)));
+    else SETD_HIP((launch_small2d<double>(g, items_dev, nitems, sub, n, d.nl, lean, s)));
     return SETD_OK;
 }
 
@@ -641,7 +650,7 @@ setd_status Plan::autotune()
     }
     const char* env = std::getenv("SETD_AUTOTUNE");
     if ((env && env[0] == '0') || no_alloc) return SETD_OK;
-    if (d.nl == NL_NONE || d.ndim == 1) return SETD_OK;   // a line has one kernel
+    if (d.nl == NL_NONE || d.ndim == 1 || small) return SETD_OK;   // a line or small lattice has one kernel
     const std::string key = tune_key(*this);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -759,6 +768,14 @@ setd_status Plan::run_steps_on(int64_t n, int split, hipStream_t s)
             if (d.precision == 32) SETD_HIP((launch_line1d<float>(g, items_dev, R, MODE_STEP, 0, c, d.nl, s)));
             else SETD_HIP((launch_line1d<double>(g, items_dev, R, MODE_STEP, 0, c, d.nl, s)));
             left -= c;
+        }
+        return SETD_OK;
+    }
+    if (small) {
+        // the state stays in LDS and registers: up to 256 steps per launch
+        for (int64_t left = n; left > 0; left -= 256) {
+            setd_status st = launch_steps(items_dev, R, 0, (int)std::min<int64_t>(left, 256), s);
+            if (st != SETD_OK) return st;
         }
         return SETD_OK;
     }
@@ -1363,7 +1380,7 @@ setd_status setd_plan_info(const setd_plan* plan, setd_plan_info_t* info)
     info->kept_modes = p.kept_modes;
     info->nbins = p.nbins;
     // an unbound plan gives the passes of the general path
-    info->passes_per_step = (p.part3 && !p.bound) ? 4 : p.passes_per_step();
+    info->passes_per_step = p.bound ? p.passes_per_step() : (p.small ? 2 : (p.part3 ? 4 : p.passes_per_step()));
     info->alg_bytes_per_step = p.alg_bytes_per_step();
     info->site_updates_per_step = (double)p.nreal * p.R;
     p.pass_bytes(info->pass_bytes);

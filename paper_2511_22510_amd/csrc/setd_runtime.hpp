@@ -86,6 +86,7 @@ struct Plan {
     // SETD2 storage: the carry Y_n = E phi_n + w_b F_{n-1} + G eta_n in the
     // F_{n-1} array, phi recovered from pre when read (phi_valid tracks it)
     bool lean = false;
+    bool small = false;           // 2D steps in one kernel (small2d_ok)
     bool part3 = false;           // 3D step in two passes (part3_ok); the line buffer holds their array
     bool phi_valid = true;
     int64_t step_host = 0;        // steps queued so far (mirror of the device counter)
@@ -103,6 +104,9 @@ struct Plan {
     // queue the passes of one step for nitems items starting at items_dev
     // (after the transform of the step's real-space noise, if the plan draws it)
     setd_status launch_step(const Item* items_dev, int nitems, int sub, hipStream_t s) const;
+    // plans whose kernel takes several steps (small): n steps from sub-step
+    // sub, each item at most its own
+    setd_status launch_steps(const Item* items_dev, int nitems, int sub, int n, hipStream_t s) const;
     // 2D/3D plans with real-space noise: its transform for the current step
     setd_status launch_noise(const Item* items_dev, int nitems, int sub, hipStream_t s) const;
     bool rsn_grid() const { return d.noise_space == 1 && d.ndim >= 2; }

@@ -290,7 +290,7 @@ setd_status setd_server::tick(std::vector<Job*>& act, int* steps_taken)
     // launch units: the classes that can share launches (one per lattice
     // size, multi2d_ok) form one unit when there are two or more of them;
     // every other class is a unit of its own (-1 marks the shared unit)
-    MultiClass mc[4] = {};
+    MultiClass mc[3] = {};
     int nshare = 0;
     if (multi)
         for (const Launch& L : launches)
@@ -322,6 +322,12 @@ setd_status setd_server::tick(std::vector<Job*>& act, int* steps_taken)
                 }
                 q_launches += 2;
                 q_shared += 2;
+            } else if (launches[units[u]].rep->small) {
+                // one launch takes all of the tick's steps
+                if (sub > 0) continue;
+                const Launch& L = launches[units[u]];
+                lst = L.rep->launch_steps(items_dev + L.first, L.n, 0, maxk, ls);
+                q_launches += 1;
             } else {
                 const Launch& L = launches[units[u]];
                 lst = L.rep->launch_step(items_dev + L.first, L.n, sub, ls);

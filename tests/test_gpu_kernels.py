@@ -86,3 +86,55 @@ def test_general_3d_step_beside_the_rule(n, kw):
     assert int(g.info.passes_per_step) == 4
     assert _trajectory_error(g, o, 1, (1, 3)) <= (1e-10 if p["precision"] == 64 else 2e-4)
     g.close()
+
+
+@pytest.mark.parametrize("n", [(64, 64), (64, 32), (32, 64), (32, 32)])
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("kind", ["a1", "b2", "kpz1", "kpz2", "b2h"])
+def test_small_lattice_kernel(n, prec, kind):
+    """Whole steps of 2D lattices of 32 and 64 points per axis in one kernel,
+    each with SETD1, the SETD2 carry and the separate SETD2 storage: steps over
+    several calls, a call of more steps than one launch takes (300), a set
+    state (restarted history) and a set step index follow the oracle to the
+    bars of the workloads."""
+    S = _setd()
+    kw = dict(precision=prec, realizations=2, seed=21, order=1 if kind.endswith("1") else 2,
+              history_readback=1 if kind == "b2h" else 0)
+    if kind.startswith("kpz"):
+        p = W.kpz(list(n), ic_kind=1, ic_sigma=0.2, **kw)
+    else:
+        p = (W.model_a if kind[0] == "a" else W.model_b)(list(n), **kw)
+    tol = 1e-10 if prec == 64 else 2e-4
+    g, o = S.Plan(p), O.Sim(p)
+    assert int(g.info.passes_per_step) == 1
+    assert _trajectory_error(g, o, 2, (1, 2, 7)) <= tol
+    x = W.random_spectrum(p, 5, 0.05)
+    g.set(1, x)
+    o.set(1, x)
+    assert _trajectory_error(g, o, 2, (1, 4)) <= tol
+    if kind == "b2h":
+        assert float(np.linalg.norm(g.history(1) - o.get(1, which=1))) <= tol * float(np.linalg.norm(o.get(1, which=1)))
+    g.set_step(1000)
+    o.set_step(1000)
+    assert _trajectory_error(g, o, 2, (3, 300)) <= (1e-9 if prec == 64 else 2e-4)
+    out = g.observe(S.OBS_STEP)
+    assert out[0] == 1303 and out[1] == 0
+    g.close()
+
+
+def test_small_lattice_jobs_take_their_own_steps():
+    """Jobs of one small launch class with different step counts share the
+    launches of a tick, each bitwise its solo run."""
+    S = _setd()
+    jobs = [(W.model_b([64, 64], realizations=3, seed=31), 40), (W.model_b([64, 64], realizations=1, seed=32), 7),
+            (W.model_a([64, 64], order=2, precision=32, seed=33), 300)]
+    srv = S.Server(64 << 20)
+    ids = [srv.submit(p, k) for p, k in jobs]
+    srv.drain()
+    for j, (p, k) in zip(ids, jobs):
+        solo = S.Plan(p)
+        solo.step(k)
+        for r in range(p["realizations"]):
+            assert np.array_equal(srv.get(j, r), solo.get(r))
+        solo.close()
+    srv.close()
