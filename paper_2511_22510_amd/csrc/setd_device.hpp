@@ -426,6 +426,13 @@ __device__ __forceinline__ void fft_line(cx<T> (&v)[8], int t, cx<T>* lds, int s
 }
 
 // ---------------------------------------------------------------- Philox
+// a ^ b ^ c in one instruction (gfx950's three-input logic operation with the
+// truth table of the parity; the compiler forms two two-input ones)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
                                               uint32_t k0, uint32_t k1)
 {
@@ -439,8 +446,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
         const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
         const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
+        const uint32_t n0 = xor3(hi1, c1, k0);
+        const uint32_t n2 = xor3(hi0, c3, k1);
         c0 = n0;
         c1 = lo1;
         c2 = n2;
@@ -522,24 +529,43 @@ __device__ __forceinline__ void box_muller32(uint32_t a, uint32_t b, double& z1,
     z2 = rad * s;
 }
 
-// Single precision, without branches: u1 < 1/2 is formed directly; for
-// u1 >= 1/2 the exactly formed om = 1 - u1 (from the complement of the word)
-// gives ln u1 by the series -om (1 + om/2 + om^2/3 + ...) when om < 1/64 and
-// by the hardware logarithm of 1 - om otherwise.
+// ln u of the uniform u = (a + 1/2) 2^-32 in single precision, without branches.
+// The smaller of u and 1 - u is formed exactly to a float's 24 bits (from the
+// word or its complement).  For u >= 1/2 the hardware logarithm takes the
+// rounded w = 1 - (1 - u), and e = u - w, exact in float, corrects it to first
+// order (ln(w + e) = ln w + e/w - .., w in [1/2, 1]).  Largest relative error
+// of sqrt(-2 ln u) against FP64: 1.7e-7; a series of -ln(1 - (1 - u)) below
+// 1/64 and the plain logarithm above, with seven more operations, had 1.0e-6.
+__device__ __forceinline__ float log_uniform32(uint32_t a)
+{
+    const bool hi = a >= 0x80000000u;
+    const float m = fmaf((float)(hi ? ~a : a), 0x1p-32f, 0x1p-33f);
+    const float w = 1.0f - m;
+    return fmaf(__builtin_amdgcn_logf(hi ? w : m), 0.69314718055994530942f, hi ? (1.0f - w) - m : 0.0f);
+}
+
 __device__ __forceinline__ void box_muller32(uint32_t a, uint32_t b, float& z1, float& z2)
 {
-    const float ln2 = 0.69314718055994530942f;
-    const bool hi = a >= 0x80000000u;
-    const float u1 = fmaf((float)a, 0x1p-32f, 0x1p-33f);
-    const float om = fmaf((float)(0xffffffffu - a), 0x1p-32f, 0x1p-33f);
-    const float p = fmaf(om, fmaf(om, fmaf(om, fmaf(om, 1.0f / 6.0f, 0.2f), 0.25f), 1.0f / 3.0f), 0.5f);
-    const float lser = -om * fmaf(om, p, 1.0f);
-    const float llog = __builtin_amdgcn_logf(hi ? 1.0f - om : u1) * ln2;
-    const float lg = (hi && om < 0.015625f) ? lser : llog;
-    const float rad = __builtin_amdgcn_sqrtf(-2.0f * lg);
+    const float rad = __builtin_amdgcn_sqrtf(-2.0f * log_uniform32(a));
     const float u2 = fmaf((float)b, 0x1p-32f, 0x1p-33f);
     z1 = rad * __builtin_amdgcn_cosf(u2);
     z2 = rad * __builtin_amdgcn_sinf(u2);
+}
+
+// (z1 + i z2)/sqrt2 of the same word pair
+__device__ __forceinline__ cx<float> box_muller_cx(uint32_t a, uint32_t b, float)
+{
+    const float rad = __builtin_amdgcn_sqrtf(-log_uniform32(a));
+    const float u2 = fmaf((float)b, 0x1p-32f, 0x1p-33f);
+    return {rad * __builtin_amdgcn_cosf(u2), rad * __builtin_amdgcn_sinf(u2)};
+}
+
+__device__ __forceinline__ cx<double> box_muller_cx(uint32_t a, uint32_t b, double)
+{
+    const double rs2 = 0.70710678118654752440084436210484903928;
+    double z1, z2;
+    box_muller32(a, b, z1, z2);
+    return {rs2 * z1, rs2 * z2};
 }
 
 // ---------------------------------------------------------------- phi functions (FP64)

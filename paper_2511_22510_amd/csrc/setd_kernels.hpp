@@ -200,11 +200,9 @@ __device__ __forceinline__ NoiseSlot noise_slot(const Geo& g, int j0, int j1, in
 template <typename T>
 __device__ __forceinline__ cx<T> eta_of(const uint32_t (&x)[4], const NoiseSlot& s)
 {
-    const T rs2 = T(0.70710678118654752440084436210484903928);
-    T z1, z2;
-    box_muller32(s.half ? x[2] : x[0], s.half ? x[3] : x[1], z1, z2);
-    if (s.kind == 1) return {z1, T(0)};
-    return {rs2 * z1, (s.kind == 2) ? -rs2 * z2 : rs2 * z2};
+    const cx<T> e = box_muller_cx(s.half ? x[2] : x[0], s.half ? x[3] : x[1], T(0));
+    if (s.kind == 1) return {T(1.41421356237309504880168872420969807857) * e.x, T(0)};
+    return {e.x, (s.kind == 2) ? -e.y : e.y};
 }
 
 // one mode (one Philox block)
@@ -2398,18 +2396,14 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
         // q div 4 of the Philox block (t + (q mod 4) M, n, r, 3)
         cx<T> e[8];
         if constexpr (RS) {
-            const T rs2 = T(0.70710678118654752440084436210484903928);
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 e[q] = e[q + 4] = czero<T>();
                 if (!act) continue;
                 uint32_t x[4];
-                T z1, z2, z3, z4;
                 philox_block(it.seed, (uint32_t)(t + q * M), (uint32_t)(step0 + s), it.r, 3u, x);
-                box_muller32(x[0], x[1], z1, z2);
-                box_muller32(x[2], x[3], z3, z4);
-                e[q] = {rs2 * z1, rs2 * z2};
-                e[q + 4] = {rs2 * z3, rs2 * z4};
+                e[q] = box_muller_cx(x[0], x[1], T(0));
+                e[q + 4] = box_muller_cx(x[2], x[3], T(0));
             }
         }
         if constexpr (KIND == 0) {

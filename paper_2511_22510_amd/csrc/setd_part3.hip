@@ -214,16 +214,12 @@ k_ax01(Part3Args a)
             }
             // noise of bins k and 7 - k from one Philox block, while the loads are in flight
             const uint32_t rest = (uint32_t)j1 * (uint32_t)g.nh_last + (uint32_t)jl;
-            const T rs2 = T(0.70710678118654752440084436210484903928);
 #pragma unroll
             for (int k = 0; k < 3; k++) {
                 uint32_t x[4];
                 philox_block(it.seed, (uint32_t)(t + k * TPL) * S + rest, nn, it.r, 0u, x);
-                T z1, z2;
-                box_muller32(x[0], x[1], z1, z2);
-                eta[k] = {rs2 * z1, rs2 * z2};
-                box_muller32(x[2], x[3], z1, z2);
-                eta[7 - k] = {rs2 * z1, rs2 * z2};
+                eta[k] = box_muller_cx(x[0], x[1], T(0));
+                eta[7 - k] = box_muller_cx(x[2], x[3], T(0));
             }
             // (the previous line's entries were last read before the barriers
             // of its inverse transform)
