@@ -419,10 +419,10 @@ __device__ __forceinline__ void fft_lines(cx<T> (&v)[NL][8], int t, cx<T>* lds, 
 }
 
 // One line held by the calling thread group.
-template <typename T, int N, int SIGN, int PAD, typename TW>
+template <typename T, int N, int SIGN, int PAD, bool WAVE = false, typename TW>
 __device__ __forceinline__ void fft_line(cx<T> (&v)[8], int t, cx<T>* lds, int stride, const TW& tw)
 {
-    fft_lines<T, N, SIGN, PAD, 1>(reinterpret_cast<cx<T>(&)[1][8]>(v), t, lds, stride, 0, tw);
+    fft_lines<T, N, SIGN, PAD, 1, WAVE>(reinterpret_cast<cx<T>(&)[1][8]>(v), t, lds, stride, 0, tw);
 }
 
 // ---------------------------------------------------------------- Philox

@@ -1949,6 +1949,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
     constexpr int LPB = 256 / TPL;
     constexpr int LL = lds_len<N, PAD>();
     constexpr int QS = DA ? 3 : (PS ? 4 : 5);    // register slots of stored modes
+    constexpr bool WV = N <= 512;                // a line lies in one wavefront
     const Geo& g = a.g;
     const int tid = threadIdx.x;
     const int l = tid / TPL, t = tid - l * TPL;
@@ -2014,7 +2015,9 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
         return;
     }
 
-    // state, F_{n-1}, coefficients and steps of both realizations
+    // state, F_{n-1}, coefficients and steps of both realizations.  The launch
+    // holds the state, F_{n-1} and G times 1/N (a power of two, so exactly):
+    // the inverse transform then gives the field itself.
     cx<T> fa[QS], fb[QS];
     Coef<T> ca[QS], cb[QS];
     const cx<T>* phia0 = reinterpret_cast<const cx<T>*>(ia.phi);
@@ -2033,14 +2036,16 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
         // a realization that does not step in this launch is no partner: its
         // channel stays zero, as for the missing partner of an odd count
         if (acta) {
-            pa[q] = phia0[m];
-            if (o2 && hpa) fa[q] = preva[m];
+            pa[q] = inv * phia0[m];
+            if (o2 && hpa) fa[q] = inv * preva[m];
             ca[q] = load_coef_t<T, false>(ia.coef, m);   // real fields: real tables, keyed by |a|
+            ca[q].G *= inv;
         }
         if (actb) {
-            pb[q] = phib0[m];
-            if (o2 && hpb) fb[q] = prevb[m];
+            pb[q] = inv * phib0[m];
+            if (o2 && hpb) fb[q] = inv * prevb[m];
             cb[q] = load_coef_t<T, false>(ib.coef, m);
+            cb[q].G *= inv;
         }
         if (m == 0 || 2 * m == N) {
             pa[q].y = T(0);
@@ -2087,7 +2092,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
     for (int s = 0; s < a.nsteps; s++) {
         if constexpr (KIND != 2) {
             // pack the two half spectra (KPZ: of h and h' per realization)
-            __syncthreads();
+            exchange_sync<WV>();
 #pragma unroll
             for (int q = 0; q < QS; q++) {
                 if (q == 4 && t != 0) continue;
@@ -2102,7 +2107,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 L[lds_slot<PAD>(m)] = A;
                 L[LL + lds_slot<PAD>(m)] = B;
             }
-            __syncthreads();
+            exchange_sync<WV>();
             cx<T> z[8];
 #pragma unroll
             for (int q = 0; q < 8; q++) {
@@ -2128,23 +2133,23 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                     w[0][q] = z[q];
                     w[1][q] = cmul(phs[q], z[q]);
                 }
-                fft_lines<T, N, +1, PAD, 2>(w, t, L, 2, 1, tw);
+                fft_lines<T, N, +1, PAD, 2, WV>(w, t, L, 2, 1, tw);
 #pragma unroll
                 for (int u = 0; u < 2; u++) {
 #pragma unroll
                     for (int q = 0; q < 8; q++) {
-                        const T x = w[u][q].x * inv, y = w[u][q].y * inv;
+                        const T x = w[u][q].x, y = w[u][q].y;
                         w[u][q] = (KIND == 1) ? cx<T>{x * x, y * y} : cx<T>{x * x * x, y * y * y};
                     }
                 }
-                fft_lines<T, N, -1, PAD, 2>(w, t, L, 2, 1, tw);
+                fft_lines<T, N, -1, PAD, 2, WV>(w, t, L, 2, 1, tw);
 #pragma unroll
                 for (int q = 0; q < 8; q++) z[q] = T(0.5) * (w[0][q] + cmulc(w[1][q], phs[q]));
             } else {
-                fft_line<T, N, +1, PAD>(z, t, L, 1, tw);
+                fft_line<T, N, +1, PAD, WV>(z, t, L, 1, tw);
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
-                    const T x = z[q].x * inv, y = z[q].y * inv;
+                    const T x = z[q].x, y = z[q].y;
                     z[q] = (KIND == 1) ? cx<T>{x * x, y * y} : cx<T>{x * x * x, y * y * y};
                 }
             }
@@ -2154,15 +2159,15 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 cx<T> e[RS ? 8 : 1];
                 if constexpr (RS) {
                     site_noise(e, s);
-                    fft_line<T, N, -1, PAD>(e, t, L, 1, tw);
+                    fft_line<T, N, -1, PAD, WV>(e, t, L, 1, tw);
                 }
-                __syncthreads();
+                exchange_sync<WV>();
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     L[lds_slot<PAD>(t + q * M)] = z[q];
                     if constexpr (RS) L[LL + lds_slot<PAD>(t + q * M)] = e[q];
                 }
-                __syncthreads();
+                exchange_sync<WV>();
             } else if constexpr (RS) {
                 // the nonlinearity and the site noise of both realizations
                 // through the forward stages together (interleaved in LDS)
@@ -2170,32 +2175,32 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 site_noise(w2[1], s);
 #pragma unroll
                 for (int q = 0; q < 8; q++) w2[0][q] = z[q];
-                fft_lines<T, N, -1, PAD, 2>(w2, t, L, 2, 1, tw);
-                __syncthreads();
+                fft_lines<T, N, -1, PAD, 2, WV>(w2, t, L, 2, 1, tw);
+                exchange_sync<WV>();
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     L[lds_slot<PAD>(t + q * M)] = w2[0][q];
                     L[LL + lds_slot<PAD>(t + q * M)] = w2[1][q];
                 }
-                __syncthreads();
+                exchange_sync<WV>();
             } else {
-                fft_line<T, N, -1, PAD>(z, t, L, 1, tw);
-                __syncthreads();
+                fft_line<T, N, -1, PAD, WV>(z, t, L, 1, tw);
+                exchange_sync<WV>();
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     if (DA && (q == 3 || q == 4)) continue;
                     L[lds_slot<PAD>(t + q * M)] = z[q];
                 }
-                __syncthreads();
+                exchange_sync<WV>();
             }
         } else if constexpr (RS) {
             cx<T> e[8];
             site_noise(e, s);
-            fft_line<T, N, -1, PAD>(e, t, L, 1, tw);
-            __syncthreads();
+            fft_line<T, N, -1, PAD, WV>(e, t, L, 1, tw);
+            exchange_sync<WV>();
 #pragma unroll
             for (int q = 0; q < 8; q++) L[LL + lds_slot<PAD>(t + q * M)] = e[q];
-            __syncthreads();
+            exchange_sync<WV>();
         }
         // split W into the two spectra with the model prefactor
         cx<T> F1[QS], F2[QS];
@@ -2205,14 +2210,15 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
             if constexpr (KIND != 2) {
                 const int k = mode_of(q) & (N - 1);
                 const cx<T> Zk = L[lds_slot<PAD>(k)], Zm = L[lds_slot<PAD>((N - k) & (N - 1))];
-                const cx<T> wa = {T(0.5) * (Zk.x + Zm.x), T(0.5) * (Zk.y - Zm.y)};
-                const cx<T> wb = {T(0.5) * (Zk.y + Zm.y), T(0.5) * (Zm.x - Zk.x)};
+                // (twice the two spectra: the half is in the factors below)
+                const cx<T> wa = {Zk.x + Zm.x, Zk.y - Zm.y};
+                const cx<T> wb = {Zk.y + Zm.y, Zm.x - Zk.x};
                 const T k2a = (dka * (T)k) * (dka * (T)k), k2b = (dkb * (T)k) * (dkb * (T)k);
                 // Model B: -u k^2; the others a constant
                 const T sa = (ia.nl == NL_PHI3_CONS) ? -(T)ia.par0 * k2a : pra.x;
                 const T sb = (ib.nl == NL_PHI3_CONS) ? -(T)ib.par0 * k2b : prb.x;
-                F1[q] = sa * wa;
-                F2[q] = sb * wb;
+                F1[q] = (T(0.5) * inv * sa) * wa;
+                F2[q] = (T(0.5) * inv * sb) * wb;
             }
         }
         cx<T> ea[QS], eb[QS];
@@ -2271,11 +2277,11 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
         for (int q = 0; q < QS; q++) {
             if (!stored(q)) continue;
             const int m = mode_of(q);
-            cx<T> na = cmul(ca[q].E, pa[q]) + cmul(ca[q].wa, F1[q]) + ca[q].G * ea[q];
-            cx<T> nb = cmul(cb[q].E, pb[q]) + cmul(cb[q].wa, F2[q]) + cb[q].G * eb[q];
+            cx<T> na = ca[q].E.x * pa[q] + ca[q].wa.x * F1[q] + ca[q].G * ea[q];
+            cx<T> nb = cb[q].E.x * pb[q] + cb[q].wa.x * F2[q] + cb[q].G * eb[q];
             if (o2) {
-                na = na + cmul(ca[q].wb, upa ? fa[q] : F1[q]);
-                nb = nb + cmul(cb[q].wb, upb ? fb[q] : F2[q]);
+                na = na + ca[q].wb.x * (upa ? fa[q] : F1[q]);
+                nb = nb + cb[q].wb.x * (upb ? fb[q] : F2[q]);
                 fa[q] = F1[q];
                 fb[q] = F2[q];
             }
@@ -2297,14 +2303,16 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
         if (!stored(q)) continue;
         const int m = mode_of(q);
         if (acta) {
-            phia[m] = pa[q];
-            if (o2 && a.nsteps > 0) pva[m] = fa[q];
-            bada |= !(isfinite(pa[q].x) && isfinite(pa[q].y));
+            const cx<T> h = T(N) * pa[q];
+            phia[m] = h;
+            if (o2 && a.nsteps > 0) pva[m] = T(N) * fa[q];
+            bada |= !(isfinite(h.x) && isfinite(h.y));
         }
         if (actb) {
-            phib[m] = pb[q];
-            if (o2 && a.nsteps > 0) pvb[m] = fb[q];
-            badb |= !(isfinite(pb[q].x) && isfinite(pb[q].y));
+            const cx<T> h = T(N) * pb[q];
+            phib[m] = h;
+            if (o2 && a.nsteps > 0) pvb[m] = T(N) * fb[q];
+            badb |= !(isfinite(h.x) && isfinite(h.y));
         }
     }
     if (bada) atomicOr(&ia.ctrl->nonfinite, 1);
@@ -2334,6 +2342,7 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
     constexpr int LPB = 256 / TPL;
+    constexpr bool WV = N <= 512;   // a line lies in one wavefront
     constexpr int LL = lds_len<N, PAD>();
     const Geo& g = a.g;
     const int tid = threadIdx.x;
@@ -2382,11 +2391,13 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
         p[q] = fp[q] = czero<T>();
         cf[q] = Coef<T>{czero<T>(), czero<T>(), czero<T>(), T(0)};
         if (si[q] < 0 || !valid) continue;
-        p[q] = phi[si[q]];
-        if (o2 && hp) fp[q] = prev0[si[q]];
+        // state, F_{n-1} and G times 1/N, as in k_line1d_real
+        p[q] = inv * phi[si[q]];
+        if (o2 && hp) fp[q] = inv * prev0[si[q]];
         cf[q] = load_coef_t<T, true>(it.coef, coef_key(it, sgn_idx(t + q * M, N), 0, 0));   // complex tables
+        cf[q].G *= inv;
     }
-    const cx<T> pref = nl_pref<T>(it, T(0));
+    const cx<T> pref = inv * nl_pref<T>(it, T(0));
     const T rsq = (T)(1.0 / sqrt((double)N));
     bool bad = false;
 #pragma unroll 1
@@ -2418,48 +2429,48 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
                     phs[q] = cispi<T>((T)sgn_idx(t + q * M, N) / (T)N);
                     z[1][q] = cmul(phs[q], p[q]);
                 }
-                fft_lines<T, N, +1, PAD, 2>(z, t, L, 2, 1, tw);
+                fft_lines<T, N, +1, PAD, 2, WV>(z, t, L, 2, 1, tw);
 #pragma unroll
                 for (int u = 0; u < 2; u++) {
 #pragma unroll
                     for (int q = 0; q < 8; q++) {
-                        const T x = z[u][q].x * inv, y = z[u][q].y * inv;
+                        const T x = z[u][q].x, y = z[u][q].y;
                         const T m2 = x * x + y * y;
                         z[u][q] = {m2 * x, m2 * y};
                     }
                 }
-                fft_lines<T, N, -1, PAD, 2>(z, t, L, 2, 1, tw);
+                fft_lines<T, N, -1, PAD, 2, WV>(z, t, L, 2, 1, tw);
 #pragma unroll
                 for (int q = 0; q < 8; q++) z[0][q] = T(0.5) * (z[0][q] + cmulc(z[1][q], phs[q]));
             } else {
-                fft_line<T, N, +1, PAD>(z[0], t, L, 1, tw);
+                fft_line<T, N, +1, PAD, WV>(z[0], t, L, 1, tw);
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
-                    const T x = z[0][q].x * inv, y = z[0][q].y * inv;
+                    const T x = z[0][q].x, y = z[0][q].y;
                     const T m2 = x * x + y * y;
                     z[0][q] = {m2 * x, m2 * y};
                 }
             }
             if constexpr (RS && PS) {
                 // the mean is already transformed: the site noise alone
-                fft_line<T, N, -1, PAD>(e, t, L, 1, tw);
+                fft_line<T, N, -1, PAD, WV>(e, t, L, 1, tw);
             } else if constexpr (RS) {
                 // the nonlinearity and the site noise through the forward
                 // stages together
 #pragma unroll
                 for (int q = 0; q < 8; q++) z[1][q] = e[q];
-                fft_lines<T, N, -1, PAD, 2>(z, t, L, 2, 1, tw);
+                fft_lines<T, N, -1, PAD, 2, WV>(z, t, L, 2, 1, tw);
 #pragma unroll
                 for (int q = 0; q < 8; q++) e[q] = z[1][q];
             } else if constexpr (!PS) {
-                fft_line<T, N, -1, PAD>(z[0], t, L, 1, tw);
+                fft_line<T, N, -1, PAD, WV>(z[0], t, L, 1, tw);
             }
 #pragma unroll
             for (int q = 0; q < 8; q++) F[q] = (si[q] >= 0) ? cmul(pref, z[0][q]) : czero<T>();
         } else {
 #pragma unroll
             for (int q = 0; q < 8; q++) F[q] = czero<T>();
-            if constexpr (RS) fft_line<T, N, -1, PAD>(e, t, L, 1, tw);
+            if constexpr (RS) fft_line<T, N, -1, PAD, WV>(e, t, L, 1, tw);
         }
         if constexpr (RS) {
 #pragma unroll
@@ -2499,9 +2510,10 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
 #pragma unroll
         for (int q = 0; q < 8; q++) {
             if (si[q] < 0) continue;
-            phi[si[q]] = p[q];
-            if (o2 && a.nsteps > 0) pv[si[q]] = fp[q];
-            bad |= !(isfinite(p[q].x) && isfinite(p[q].y));
+            const cx<T> h = T(N) * p[q];
+            phi[si[q]] = h;
+            if (o2 && a.nsteps > 0) pv[si[q]] = T(N) * fp[q];
+            bad |= !(isfinite(h.x) && isfinite(h.y));
         }
     }
     if (bad) atomicOr(&it.ctrl->nonfinite, 1);
