@@ -168,8 +168,9 @@ k_ax01(Part3Args a)
     int64_t nstep = 0;
     int hp = 0;
     if constexpr (MODE == MODE_STEP) {
-        nstep = *(const SETD_GLOBAL int64_t*)&it.ctrl->step;
-        hp = *(const SETD_GLOBAL int*)&it.ctrl->have_prev;
+        // the row pass has begun the step
+        nstep = *(const SETD_GLOBAL int64_t*)&it.ctrl->step - 1;
+        hp = *(const SETD_GLOBAL int*)&it.ctrl->have_prev >= 2;
     }
     const uint32_t nn = (uint32_t)(nstep + 1);   // the carry holds the next step's noise
     const rsrc_t rcoef = make_rsrc(it.coef, it.coef_bytes);
@@ -288,7 +289,6 @@ k_ax01(Part3Args a)
     if constexpr (MODE == MODE_STEP) {
         const bool bad = !(nfacc == nfacc);
         if (__syncthreads_or(bad) && tid == 0) atomicOr(&it.ctrl->nonfinite, 1);
-        if (tid == 0) advance_step(it.ctrl, (unsigned)a.per_item, nstep);
     }
 }
 
@@ -309,6 +309,7 @@ k_rows32(Part3Args a)
     const int blk = (int)(lg % (unsigned)a.per_item);
     const Item it = a.items[item];
     if (a.sub >= it.steps) return;
+    if (blk == 0 && threadIdx.x == 0) begin_step(it.ctrl);
     constexpr int NT = rows32_threads<N2>(), TPL = N2 / 8, PAD = 3;
     constexpr int K = (N2 - 1) / 3, KL = 2 * K + 1;      // stored columns
     constexpr int G = NT / TPL, NP = 32 / G;             // rows at a time, rounds
