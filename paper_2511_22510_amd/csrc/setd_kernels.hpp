@@ -1916,6 +1916,7 @@ struct Line1dArgs {
     int mode;     // MODE_STEP or MODE_IC
     int sub;      // sub-step of the scheduler tick
     int nsteps;   // MODE_STEP: steps of this launch
+    Record rec;   // MODE_STEP: the time-series window, if one is open
 };
 
 // Twiddles of a line kernel: every power in registers (FP32) or the stage
@@ -2297,6 +2298,11 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
             }
             if (acta) pa[q] = na;
             if (actb) pb[q] = nb;
+            if (a.rec.slot) {
+                const int64_t o = a.rec.first + s * a.rec.slot;
+                if (acta) reinterpret_cast<cx<T>*>((char*)ia.phi + o)[m] = T(N) * na;
+                if (actb) reinterpret_cast<cx<T>*>((char*)ib.phi + o)[m] = T(N) * nb;
+            }
         }
     }
     cx<T>* phia = reinterpret_cast<cx<T>*>(ia.phi);
@@ -2509,6 +2515,8 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
                 fp[q] = F[q];
             }
             if (act) p[q] = nw;
+            if (act && a.rec.slot)
+                reinterpret_cast<cx<T>*>((char*)it.phi + a.rec.first + s * a.rec.slot)[si[q]] = T(N) * nw;
         }
     }
     cx<T>* pv = reinterpret_cast<cx<T>*>(it.prev);
@@ -2660,11 +2668,17 @@ static __global__ void __launch_bounds__(256) k_boxfinal(BoxArgs a, size_t ncls)
 
 // ---------------------------------------------------------------- time-frequency observables (App. C)
 
-// One line per (stored mode, realization): the window phi_a(m) and the kicks
+// One line per stored mode: for each of the block's realizations in turn, the
+// window phi_a(m) and the kicks
 // xi_a(m) = G_a eta_a(n0 + m) of the steps taken from the samples go through
 // the unscaled transform with e^{+2 pi i b m / M} together; an interior mode
 // of a real field adds its mirror -a (the conjugate transforms at -w_b, read
-// back through LDS); FP64 sums per shell and frequency.
+// back through LDS); FP64 sums over the block's realizations in registers, then
+// per shell and frequency in memory.  (One block per realization, with three
+// FP64 atomics per mode, frequency and realization, was bound by the atomics:
+// filling a window of 256 samples of a line N = 256 x 1024 realizations and its
+// spectrum and FDT deviation, with the samples stored by the line kernel: 4.06
+// -> 1.47 ms.)
 template <typename T, int M, int PAD>
 __global__ void __launch_bounds__(256) k_spectrum(SpecArgs a)
 {
@@ -2676,7 +2690,8 @@ __global__ void __launch_bounds__(256) k_spectrum(SpecArgs a)
     const int lpb = (int)blockDim.x / TPL;
     const int l = tid / TPL, t = tid - l * TPL;
     const int idx = blockIdx.x * lpb + l;     // stored element of the realization
-    const Item& it = a.items[blockIdx.y];
+    const int r0 = (int)blockIdx.y * a.rper, r1 = min(r0 + a.rper, a.nitems);
+    const Item& it = a.items[r0];   // the realizations of a plan share tables and lattice
     const Geo& g = a.g;
     const int last = g.ndim - 1;
     cx<T>* L = lds + l * 2 * LL;
@@ -2712,30 +2727,59 @@ __global__ void __launch_bounds__(256) k_spectrum(SpecArgs a)
     const double w = (!g.cplx && col > 0 && 2 * col < g.n[last]) ? 2.0 : 1.0;
     const int shell = ceil_isqrt(a0 * a0 + a1 * a1 + al * al);
 
-    cx<T> v[2][8];
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-        const int m = t + q * TPL;
-        v[0][q] = czero<T>();
-        v[1][q] = czero<T>();
-        if (use) {
-            v[0][q] = *reinterpret_cast<const cx<T>*>(a.series + (size_t)m * a.slot + (size_t)blockIdx.y * a.rstride +
-                                                      (size_t)idx * sizeof(cx<T>));
-            const cx<T> e = noise_eta<T>(g, it, j0, j1, jl, (uint32_t)(a.step0 + m));
-            v[1][q] = {(T)G * e.x, (T)G * e.y};
-        }
-    }
     LineTw<T, M> tw;
     line_tw_load(tw, t, reinterpret_cast<const cx<T>*>(a.tw));
-    fft_lines<T, M, +1, PAD, 2>(v, t, L, 1, LL, tw);
-    // the transforms at -w_b for the mirror of an interior real mode
-    __syncthreads();
+    double c2s[8], xrs[8], xis[8], dvs[8];
 #pragma unroll
-    for (int q = 0; q < 8; q++) {
-        L[lds_slot<PAD>(t + q * TPL)] = v[0][q];
-        L[LL + lds_slot<PAD>(t + q * TPL)] = v[1][q];
+    for (int q = 0; q < 8; q++) c2s[q] = xrs[q] = xis[q] = dvs[q] = 0.0;
+#pragma unroll 1
+    for (int r = r0; r < r1; r++) {
+        cx<T> v[2][8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const int m = t + q * TPL;
+            v[0][q] = czero<T>();
+            v[1][q] = czero<T>();
+            if (use) {
+                v[0][q] = *reinterpret_cast<const cx<T>*>(a.series + (size_t)m * a.slot + (size_t)r * a.rstride +
+                                                          (size_t)idx * sizeof(cx<T>));
+                const cx<T> e = noise_eta<T>(g, a.items[r], j0, j1, jl, (uint32_t)(a.step0 + m));
+                v[1][q] = {(T)G * e.x, (T)G * e.y};
+            }
+        }
+        fft_lines<T, M, +1, PAD, 2>(v, t, L, 1, LL, tw);
+        // the transforms at -w_b for the mirror of an interior real mode
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            L[lds_slot<PAD>(t + q * TPL)] = v[0][q];
+            L[LL + lds_slot<PAD>(t + q * TPL)] = v[1][q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const int b = t + q * TPL;
+            const double px = v[0][q].x, py = v[0][q].y, xx = v[1][q].x, xy = v[1][q].y;
+            double c2 = px * px + py * py;
+            double xr = px * xx + py * xy, xi = py * xx - px * xy;   // phi conj(xi)
+            // FDT check (Sec. 5): 2 Im chi - (w_b / D_a) C of this mode (its own
+            // frequencies; the mirror of an interior mode is counted at the end),
+            // w_b h = 2 pi b / M with b signed
+            if (a.dacc) dvs[q] += xi - 6.283185307179586476925 * (double)(2 * b < M ? b : b - M) / (double)M * c2;
+            if (w == 2.0) {
+                const int bm = (M - b) & (M - 1);
+                const cx<T> pm = L[lds_slot<PAD>(bm)], km = L[LL + lds_slot<PAD>(bm)];
+                const double qx = pm.x, qy = pm.y, yx = km.x, yy = km.y;
+                c2 += qx * qx + qy * qy;
+                xr += qx * yx + qy * yy;         // conj(phi(-b) conj xi(-b))
+                xi -= qy * yx - qx * yy;
+            }
+            c2s[q] += c2;
+            xrs[q] += xr;
+            xis[q] += xi;
+        }
+        if constexpr (FftPlan<M>::NST == 1) __syncthreads();   // (longer windows: the next exchange's barrier)
     }
-    __syncthreads();
     if (!use) return;   // no barrier follows
     const int nb = a.nbins;
     const double invR = 1.0 / (double)a.nitems;
@@ -2743,28 +2787,10 @@ __global__ void __launch_bounds__(256) k_spectrum(SpecArgs a)
 #pragma unroll
     for (int q = 0; q < 8; q++) {
         const int b = t + q * TPL;
-        const double px = v[0][q].x, py = v[0][q].y, xx = v[1][q].x, xy = v[1][q].y;
-        double c2 = px * px + py * py;
-        double xr = px * xx + py * xy, xi = py * xx - px * xy;   // phi conj(xi)
-        if (a.dacc) {
-            // FDT check (Sec. 5): 2 Im chi - (w_b / D_a) C of this mode (its own
-            // frequencies; the mirror of an interior mode is counted at the end),
-            // w_b h = 2 pi b / M with b signed
-            const int bs = (2 * b < M) ? b : b - M;
-            const double wh = 6.283185307179586476925 * (double)bs / (double)M;
-            atomicAdd(&a.dacc[(size_t)idx * M + b], a.vol / (Da * M) * invR * (xi - wh * c2));
-        }
-        if (w == 2.0) {
-            const int bm = (M - b) & (M - 1);
-            const cx<T> pm = L[lds_slot<PAD>(bm)], km = L[LL + lds_slot<PAD>(bm)];
-            const double qx = pm.x, qy = pm.y, yx = km.x, yy = km.y;
-            c2 += qx * qx + qy * qy;
-            xr += qx * yx + qy * yy;         // conj(phi(-b) conj xi(-b))
-            xi -= qy * yx - qx * yy;
-        }
-        atomicAdd(&a.acc[(size_t)shell * M + b], cC * c2);
-        atomicAdd(&a.acc[((size_t)nb + shell) * M + b], cX * xr);
-        atomicAdd(&a.acc[((size_t)2 * nb + shell) * M + b], cX * xi);
+        if (a.dacc) atomicAdd(&a.dacc[(size_t)idx * M + b], a.vol / (Da * M) * invR * dvs[q]);
+        atomicAdd(&a.acc[(size_t)shell * M + b], cC * c2s[q]);
+        atomicAdd(&a.acc[((size_t)nb + shell) * M + b], cX * xrs[q]);
+        atomicAdd(&a.acc[((size_t)2 * nb + shell) * M + b], cX * xis[q]);
     }
     if (blockIdx.y == 0 && t == 0) atomicAdd(&a.acc[(size_t)3 * nb * M + shell], w);
 }

@@ -98,11 +98,11 @@ inline bool small2d_ok(const Geo& g, int nl)
 }
 template <typename T>
 hipError_t launch_small2d(const Geo& g, const Item* items, int nitems, int sub, int nsteps, int nl, bool lean,
-                          hipStream_t s);
+                          const Record& rec, hipStream_t s);
 // 1D lattices: nsteps steps per launch (MODE_STEP) or the initial condition (MODE_IC)
 template <typename T>
 hipError_t launch_line1d(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps, int nl,
-                         hipStream_t s);
+                         const Record& rec, hipStream_t s);
 // box-averaged width: class sums of one realization, then sum_c |A_c|^2 per level
 template <typename T>
 hipError_t launch_boxwidth(const BoxArgs& a, size_t ncls, hipStream_t s);

@@ -445,7 +445,7 @@ hipError_t launch_linear(const Geo& g, const Item* items, int nitems, int sub, i
 // condition (MODE_IC)
 template <typename T, int N, int DM, bool RS>
 static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps,
-                                  int nl, hipStream_t s)
+                                  int nl, const Record& rec, hipStream_t s)
 {
     // FP32 lines pad LDS by one slot per 8 (fewer bank conflicts in the
     // exchanges); FP64 lines would exceed 64 KiB of LDS with it
@@ -458,6 +458,7 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
     a.mode = mode;
     a.sub = sub;
     a.nsteps = nsteps;
+    a.rec = rec;
     if (g.cplx) {
         a.nlines = nitems;
         const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
@@ -477,22 +478,22 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
 
 template <typename T>
 hipError_t launch_line1d(const Geo& g, const Item* items, int nitems, int mode, int sub, int nsteps, int nl,
-                         hipStream_t s)
+                         const Record& rec, hipStream_t s)
 {
     if (g.ndim != 1 || nitems <= 0) return hipErrorInvalidValue;
     // dealias 0 none, 1 the 2/3 rule, 2 phase shift
     if (g.dealias == 2 && g.rsn) {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 2, true>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 2, true>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     } else if (g.dealias == 1 && g.rsn) {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 1, true>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 1, true>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     } else if (g.dealias == 1) {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 1, false>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 1, false>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     } else if (g.dealias == 2) {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 2, false>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 2, false>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     } else if (g.rsn) {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 0, true>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 0, true>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     } else {
-        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 0, false>(g, items, nitems, mode, sub, nsteps, nl, s)));
+        SETD_DISPATCH_N(g.n[0], return (launch_line1d_n<T, NN, 0, false>(g, items, nitems, mode, sub, nsteps, nl, rec, s)));
     }
     return hipErrorInvalidValue;
 }
@@ -518,7 +519,12 @@ static hipError_t launch_spectrum_m(const SpecArgs& a0, hipStream_t s)
     constexpr int PAD = 3;
     constexpr int tpl = M / 8;
     const int lpb = tpl >= 256 ? 1 : 256 / tpl;
-    dim3 grid((a.total + lpb - 1) / lpb, a.nitems);
+    // as many realizations per block as leave about four blocks per CU, at
+    // most 64 (the registers sum them before the atomics)
+    const int lines = (a.total + lpb - 1) / lpb;
+    a.rper = (int)(((long)lines * a.nitems) / 1024);
+    a.rper = a.rper < 1 ? 1 : (a.rper > 64 ? 64 : a.rper);
+    dim3 grid(lines, (a.nitems + a.rper - 1) / a.rper);
     const size_t lds = (size_t)lpb * 2 * lds_len<M, PAD>() * 2 * sizeof(T);
     hipLaunchKernelGGL((k_spectrum<T, M, PAD>), grid, dim3(lpb * tpl), lds, s, a);
     return hipGetLastError();
@@ -577,6 +583,6 @@ hipError_t launch_observe(const Geo& g, const Item* items, int nitems, int kind,
 // the 1D line kernels, in translation units of their own (they compile in
 // parallel with the others)
 #define SETD_INSTANTIATE_LINES(T) \
-    template hipError_t launch_line1d<T>(const Geo&, const Item*, int, int, int, int, int, hipStream_t);
+    template hipError_t launch_line1d<T>(const Geo&, const Item*, int, int, int, int, int, const Record&, hipStream_t);
 
 }  // namespace setd

@@ -337,10 +337,6 @@ template <typename T>
 static setd_status launch_pass_t(const Plan& p, int i, const Item* items_dev, int nitems, int sub, hipStream_t s)
 {
     const Geo& g = p.g;
-    if (g.ndim == 1) {
-        SETD_HIP((launch_line1d<T>(g, items_dev, nitems, MODE_STEP, sub, 1, p.d.nl, s)));
-        return SETD_OK;
-    }
     if (p.d.nl == NL_NONE) {
         SETD_HIP((launch_linear<T>(g, items_dev, nitems, sub, LIN_STEP, 0, s)));
         return SETD_OK;
@@ -368,7 +364,7 @@ static setd_status launch_pass_t(const Plan& p, int i, const Item* items_dev, in
 
 setd_status Plan::launch_pass(int i, const Item* items_dev, int nitems, int sub, hipStream_t s) const
 {
-    if (small) return launch_steps(items_dev, nitems, sub, 1, s);
+    if (multi_step()) return launch_steps(items_dev, nitems, sub, 1, Record{0, 0}, s);
     return d.precision == 32 ? launch_pass_t<float>(*this, i, items_dev, nitems, sub, s)
                              : launch_pass_t<double>(*this, i, items_dev, nitems, sub, s);
 }
@@ -381,10 +377,17 @@ setd_status Plan::launch_noise(const Item* items_dev, int nitems, int sub, hipSt
     return SETD_OK;
 }
 
-setd_status Plan::launch_steps(const Item* items_dev, int nitems, int sub, int n, hipStream_t s) const
+setd_status Plan::launch_steps(const Item* items_dev, int nitems, int sub, int n, const Record& rec,
+                               hipStream_t s) const
 {
-    if (d.precision == 32) SETD_HIP((launch_small2d<float>(g, items_dev, nitems, sub, n, d.nl, lean, s)));
-    else SETD_HIP((launch_small2d<double>(g, items_dev, nitems, sub, n, d.nl, lean, s)));
+    const bool f32 = d.precision == 32;
+    if (d.ndim == 1) {
+        if (f32) SETD_HIP((launch_line1d<float>(g, items_dev, nitems, MODE_STEP, sub, n, d.nl, rec, s)));
+        else SETD_HIP((launch_line1d<double>(g, items_dev, nitems, MODE_STEP, sub, n, d.nl, rec, s)));
+    } else {
+        if (f32) SETD_HIP((launch_small2d<float>(g, items_dev, nitems, sub, n, d.nl, lean, rec, s)));
+        else SETD_HIP((launch_small2d<double>(g, items_dev, nitems, sub, n, d.nl, lean, rec, s)));
+    }
     return SETD_OK;
 }
 
@@ -404,7 +407,7 @@ static setd_status launch_ic_t(const Plan& p, const Item* items_dev, int nitems,
 {
     const Geo& g = p.g;
     if (g.ndim == 1) {
-        SETD_HIP((launch_line1d<T>(g, items_dev, nitems, MODE_IC, 0, 0, p.d.nl, s)));
+        SETD_HIP((launch_line1d<T>(g, items_dev, nitems, MODE_IC, 0, 0, p.d.nl, Record{0, 0}, s)));
         return SETD_OK;
     }
     SETD_HIP((launch_row<T>(g, items_dev, nitems, MODE_IC, 0, p.tune.row, 0, s)));
@@ -761,20 +764,10 @@ setd_status Plan::autotune()
 setd_status Plan::run_steps_on(int64_t n, int split, hipStream_t s)
 {
     const Item* items_dev = reinterpret_cast<const Item*>(ws + lay.items);
-    if (g.ndim == 1) {
-        // a line steps in registers: up to 256 steps per launch
-        for (int64_t left = n; left > 0;) {
-            const int c = (int)std::min<int64_t>(left, 256);
-            if (d.precision == 32) SETD_HIP((launch_line1d<float>(g, items_dev, R, MODE_STEP, 0, c, d.nl, s)));
-            else SETD_HIP((launch_line1d<double>(g, items_dev, R, MODE_STEP, 0, c, d.nl, s)));
-            left -= c;
-        }
-        return SETD_OK;
-    }
-    if (small) {
-        // the state stays in LDS and registers: up to 256 steps per launch
+    if (multi_step()) {
+        // the state stays in registers (and LDS): up to 256 steps per launch
         for (int64_t left = n; left > 0; left -= 256) {
-            setd_status st = launch_steps(items_dev, R, 0, (int)std::min<int64_t>(left, 256), s);
+            setd_status st = launch_steps(items_dev, R, 0, (int)std::min<int64_t>(left, 256), Record{0, 0}, s);
             if (st != SETD_OK) return st;
         }
         return SETD_OK;
@@ -864,7 +857,18 @@ setd_status Plan::step(int64_t n)
     if (step_host + n >= (int64_t)1 << 32) return fail(SETD_E_INVAL, "step index would exceed 2^32");
     const Item* items_dev = reinterpret_cast<const Item*>(ws + lay.items);
     if (n > 0) phi_valid = !lean;
-    // an open time-series window takes a sample after every step
+    // an open time-series window takes a sample after every step; kernels of
+    // several steps store the samples themselves
+    while (n > 0 && multi_step() && series_pos >= 0 && series_pos < d.series_len) {
+        const int k = (int)std::min<int64_t>(std::min<int64_t>(n, 256), d.series_len - series_pos);
+        const int64_t slot = (int64_t)((size_t)R * Sb);
+        const Record rec = {(int64_t)lay.series - (int64_t)lay.phi + series_pos * slot, slot};
+        setd_status st = launch_steps(items_dev, R, 0, k, rec, stream);
+        if (st != SETD_OK) return st;
+        series_pos += k;
+        step_host += k;
+        n -= k;
+    }
     while (n > 0 && series_pos >= 0 && series_pos < d.series_len) {
         setd_status st = run_steps(1, 1);
         if (st != SETD_OK) return st;

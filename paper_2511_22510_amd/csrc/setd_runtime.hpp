@@ -104,9 +104,11 @@ struct Plan {
     // queue the passes of one step for nitems items starting at items_dev
     // (after the transform of the step's real-space noise, if the plan draws it)
     setd_status launch_step(const Item* items_dev, int nitems, int sub, hipStream_t s) const;
-    // plans whose kernel takes several steps (small): n steps from sub-step
-    // sub, each item at most its own
-    setd_status launch_steps(const Item* items_dev, int nitems, int sub, int n, hipStream_t s) const;
+    // plans whose kernel takes several steps (multi_step: lines and small
+    // lattices): n steps from sub-step sub (small lattices: each item at most
+    // its own), recording the time-series window rec
+    setd_status launch_steps(const Item* items_dev, int nitems, int sub, int n, const Record& rec, hipStream_t s) const;
+    bool multi_step() const { return d.ndim == 1 || small; }
     // 2D/3D plans with real-space noise: its transform for the current step
     setd_status launch_noise(const Item* items_dev, int nitems, int sub, hipStream_t s) const;
     bool rsn_grid() const { return d.noise_space == 1 && d.ndim >= 2; }

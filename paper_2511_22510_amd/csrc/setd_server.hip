@@ -326,7 +326,7 @@ setd_status setd_server::tick(std::vector<Job*>& act, int* steps_taken)
                 // one launch takes all of the tick's steps
                 if (sub > 0) continue;
                 const Launch& L = launches[units[u]];
-                lst = L.rep->launch_steps(items_dev + L.first, L.n, 0, maxk, ls);
+                lst = L.rep->launch_steps(items_dev + L.first, L.n, 0, maxk, Record{0, 0}, ls);
                 q_launches += 1;
             } else {
                 const Launch& L = launches[units[u]];

@@ -1,5 +1,5 @@
 #include "setd_small_impl.hpp"
 
 namespace setd {
-template hipError_t launch_small2d<double>(const Geo&, const Item*, int, int, int, int, bool, hipStream_t);
+template hipError_t launch_small2d<double>(const Geo&, const Item*, int, int, int, int, bool, const Record&, hipStream_t);
 }

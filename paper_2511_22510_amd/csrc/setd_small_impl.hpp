@@ -29,6 +29,7 @@ struct SmallArgs {
     const Item* items;
     int sub;      // first sub-step of the scheduler tick
     int nsteps;   // steps of this launch (each item at most its own steps)
+    Record rec;   // the time-series window, if one is open
 };
 
 template <typename T, int N0, int N1, bool KPZ>
@@ -286,6 +287,12 @@ __global__ void __launch_bounds__((SmallShape<T, N0, N1, KPZ>::THREADS)) k_small
                     }
                 }
             }
+            if (a.rec.slot && cv) {
+                cx<T>* const smp = reinterpret_cast<cx<T>*>((char*)it.phi + a.rec.first + s * a.rec.slot);
+#pragma unroll
+                for (int u = 0; u < 6; u++)
+                    if (stored(bin(u), t)) smp[sidx(u)] = v[0][bin(u)];
+            }
             cx<T> v2[1][8];
             if constexpr (KPZ) {
 #pragma unroll
@@ -334,9 +341,9 @@ __global__ void __launch_bounds__((SmallShape<T, N0, N1, KPZ>::THREADS)) k_small
 
 template <typename T, int N0, int N1>
 static hipError_t launch_small_n(const Geo& g, const Item* items, int nitems, int sub, int nsteps, bool kpz, bool lean,
-                                 hipStream_t s)
+                                 const Record& rec, hipStream_t s)
 {
-    const SmallArgs a = {g, items, sub, nsteps};
+    const SmallArgs a = {g, items, sub, nsteps, rec};
     const dim3 grid(nitems);
     const dim3 bk(SmallShape<T, N0, N1, true>::THREADS), bp(SmallShape<T, N0, N1, false>::THREADS);
     if (kpz && lean) hipLaunchKernelGGL((k_small2d<T, N0, N1, true, true>), grid, bk, 0, s, a);
@@ -348,14 +355,14 @@ static hipError_t launch_small_n(const Geo& g, const Item* items, int nitems, in
 
 template <typename T>
 hipError_t launch_small2d(const Geo& g, const Item* items, int nitems, int sub, int nsteps, int nl, bool lean,
-                          hipStream_t s)
+                          const Record& rec, hipStream_t s)
 {
     const bool kpz = nl == NL_KPZ;
     if (!small2d_ok(g, nl) || nitems <= 0) return hipErrorInvalidValue;
-    if (g.n[0] == 64 && g.n[1] == 64) return launch_small_n<T, 64, 64>(g, items, nitems, sub, nsteps, kpz, lean, s);
-    if (g.n[0] == 64) return launch_small_n<T, 64, 32>(g, items, nitems, sub, nsteps, kpz, lean, s);
-    if (g.n[1] == 64) return launch_small_n<T, 32, 64>(g, items, nitems, sub, nsteps, kpz, lean, s);
-    return launch_small_n<T, 32, 32>(g, items, nitems, sub, nsteps, kpz, lean, s);
+    if (g.n[0] == 64 && g.n[1] == 64) return launch_small_n<T, 64, 64>(g, items, nitems, sub, nsteps, kpz, lean, rec, s);
+    if (g.n[0] == 64) return launch_small_n<T, 64, 32>(g, items, nitems, sub, nsteps, kpz, lean, rec, s);
+    if (g.n[1] == 64) return launch_small_n<T, 32, 64>(g, items, nitems, sub, nsteps, kpz, lean, rec, s);
+    return launch_small_n<T, 32, 32>(g, items, nitems, sub, nsteps, kpz, lean, rec, s);
 }
 
 }  // namespace setd

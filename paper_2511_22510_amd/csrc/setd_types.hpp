@@ -70,6 +70,15 @@ struct Item {
     double ic_sigma;
 };
 
+// A time-series window recorded by kernels that take several steps per launch:
+// the stored spectrum after step s of the launch goes first + s slot bytes past
+// the item's phi (a sample holds every realization's spectrum at the distances
+// of the phi array).  slot 0: nothing is recorded.
+struct Record {
+    int64_t first;
+    int64_t slot;
+};
+
 // arguments of the FP64 coefficient-table kernel
 struct CoefArgs {
     int nkeys, mode, ndim, order, kpow, cplx_table;
@@ -100,6 +109,7 @@ struct SpecArgs {
     Geo g;
     const Item* items;
     int nitems, nbins, total;     // total: stored elements per realization
+    int rper;                     // realizations of a block (set by the launcher)
     const char* series;           // sample m of realization r at series + m * slot + r * rstride
     size_t slot, rstride;
     const void* tw;               // exp(-2 pi i k / M), state precision

@@ -138,3 +138,44 @@ def test_small_lattice_jobs_take_their_own_steps():
             assert np.array_equal(srv.get(j, r), solo.get(r))
         solo.close()
     srv.close()
+
+
+@pytest.mark.parametrize("p,M,calls", [
+    (W.model_a([64], precision=64, realizations=2101, seed=41, dx=0.5), 64, (10, 53)),
+    (W.model_a([8], precision=32, realizations=4099, seed=42, order=2), 8, (7,)),
+    (W.cgl([32], precision=32, realizations=3, seed=43, ic_sigma=0.3), 512, (300, 211)),
+    (W.model_b([32, 64], precision=64, realizations=3, seed=44), 16, (1, 14)),
+    (W.model_a([64, 64], precision=32, realizations=2, seed=45, order=2, history_readback=1), 8, (7,)),
+    (W.kpz([32, 32], precision=32, realizations=9, seed=46, ic_kind=1, ic_sigma=0.2), 32, (20, 20)),
+])
+def test_windows_recorded_by_the_step_kernels(p, M, calls):
+    """Windows whose samples the line and small-lattice kernels store
+    themselves, filled over several calls (the last one past its end, a window
+    longer than a launch's 256 steps among them), and their sums over several
+    realizations per block: C, chi and the FDT deviation against the oracle, to
+    the bars of the workloads (the sums are means over thousands of values of
+    both signs, compared to the largest one)."""
+    S = _setd()
+    p = dict(p, series_len=M)
+    g, o = S.Plan(p), O.Sim(p)
+    g.step(2)
+    o.step(2)
+    g.observe(S.OBS_SERIES_START)
+    o.series_start(M)
+    for n in calls:
+        g.step(n)
+        o.step(n)
+    tol = 1e-10 if p["precision"] == 64 else 2e-4
+    got = g.observe(S.OBS_SPECTRUM) if p["n"][0] == p["n"][-1] else None
+    if got is not None:
+        C, xr, xi, cnt = g.spectrum()
+        oC, oxr, oxi, ocnt = o.spectrum()
+        assert np.array_equal(cnt, ocnt)
+        for a, b in ((C, oC), (xr, oxr), (xi, oxi)):
+            assert float(np.max(np.abs(a - b))) <= tol * float(np.max(np.abs(b)))
+    a, b = g.fdt(), o.fdt()
+    assert abs(a[0] - b[0]) <= (1e-10 if p["precision"] == 64 else 1e-3) * b[0]
+    assert abs(a[1] - b[1]) <= (1e-10 if p["precision"] == 64 else 1e-3) * b[0]
+    for r in range(min(3, p["realizations"])):
+        assert float(np.linalg.norm(g.get(r) - o.get(r))) <= tol * float(np.linalg.norm(o.get(r)))
+    g.close()
