@@ -328,6 +328,7 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
     cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
     if (KIND != 2 && bx == 0 && sel == 0 && tid == 0) begin_step(it.ctrl);
     constexpr int TPL = N / 8;
+    constexpr bool WV = N <= 512;   // a line lies in one wavefront
     constexpr uint32_t ES = sizeof(cx<T>);
     const int l = tid / TPL, t = tid - l * TPL;
     // KPZ and phase-shift steps hold two lines per row pair in LDS, KPZ with
@@ -445,9 +446,9 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                     if (empty(q)) {
                     } else if (lower(q)) {
                         cx<T> Aq = A[s][q];
-                        const T kk = (2 * k == N) ? T(0) : dkl * (T)k;
+                        const T kk = (!DA && 2 * k == N) ? T(0) : dkl * (T)k;
                         cx<T> B = {-kk * X[s][q].y, kk * X[s][q].x};
-                        if (k == 0 || 2 * k == N) {
+                        if ((!DA || q == 0) && (k == 0 || (!DA && 2 * k == N))) {
                             Aq.y = T(0);
                             B.y = T(0);
                         }
@@ -476,7 +477,7 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                         w4[2 + s][q] = cmul(phs[q], w[s][q]);
                     }
                 }
-                fft_lines<T, N, +1, PAD, 4>(w4, t, L, 4, 1, twp);
+                fft_lines<T, N, +1, PAD, 4, WV>(w4, t, L, 4, 1, twp);
                 cx<T> sq[2][8];
 #pragma unroll
                 for (int u = 0; u < 2; u++) {
@@ -487,11 +488,11 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                         sq[u][q] = {x0 * x0 + y0 * y0, x1 * x1 + y1 * y1};
                     }
                 }
-                fft_lines<T, N, -1, PAD, 2>(sq, t, L, 2, 1, twp);
+                fft_lines<T, N, -1, PAD, 2, WV>(sq, t, L, 2, 1, twp);
 #pragma unroll
                 for (int q = 0; q < 8; q++) v[q] = T(0.5) * (sq[0][q] + cmulc(sq[1][q], phs[q]));
             } else {
-                fft_lines<T, N, +1, PAD, 2>(w, t, L, 2, 1, twp);
+                fft_lines<T, N, +1, PAD, 2, WV>(w, t, L, 2, 1, twp);
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     const T x0 = w[0][q].x * inv, y0 = w[0][q].y * inv;
@@ -508,7 +509,7 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                     z = czero<T>();
                 } else if (lower(q)) {
                     cx<T> a0 = A[0][q], b0 = A[1][q];
-                    if (k == 0 || 2 * k == N) {
+                    if ((!DA || q == 0) && (k == 0 || (!DA && 2 * k == N))) {
                         a0.y = T(0);
                         b0.y = T(0);
                     }
@@ -531,7 +532,7 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                     w[0][q] = v[q];
                     w[1][q] = cmul(phs[q], v[q]);
                 }
-                fft_lines<T, N, +1, PAD, 2>(w, t, L, 2, 1, twp);
+                fft_lines<T, N, +1, PAD, 2, WV>(w, t, L, 2, 1, twp);
 #pragma unroll
                 for (int u = 0; u < 2; u++) {
 #pragma unroll
@@ -540,11 +541,11 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
                         w[u][q] = {x * x * x, y * y * y};
                     }
                 }
-                fft_lines<T, N, -1, PAD, 2>(w, t, L, 2, 1, twp);
+                fft_lines<T, N, -1, PAD, 2, WV>(w, t, L, 2, 1, twp);
 #pragma unroll
                 for (int q = 0; q < 8; q++) v[q] = T(0.5) * (w[0][q] + cmulc(w[1][q], phs[q]));
             } else {
-                fft_line<T, N, +1, PAD>(v, t, L, 1, twp);
+                fft_line<T, N, +1, PAD, WV>(v, t, L, 1, twp);
                 // phi^3 in real space (Model A and B)
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
@@ -554,15 +555,15 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
             }
         }
 
-        if constexpr (KIND != 3 && KIND != 4) fft_line<T, N, -1, PAD>(v, t, L, 1, twp);
-        __syncthreads();
+        if constexpr (KIND != 3 && KIND != 4) fft_line<T, N, -1, PAD, WV>(v, t, L, 1, twp);
+        exchange_sync<WV>();
 #pragma unroll
         for (int q = 0; q < 8; q++) {
             // under the 2/3 rule the split below reads bins k < 3N/8 and N - k > 5N/8 only
             if (DA && (q == 3 || q == 4)) continue;
             L[lds_slot<PAD>(t + q * TPL)] = v[q];
         }
-        __syncthreads();
+        exchange_sync<WV>();
 #pragma unroll
         for (int q = 0; q < 8; q++) {
             // under the 2/3 rule only q <= 2 (k < 3N/8) can hold a stored mode
@@ -570,8 +571,13 @@ __device__ __forceinline__ void row_real_body(const RowArgs& a, const int bx, co
             const int k = t + q * TPL;
             const cx<T> Zk = L[lds_slot<PAD>(k)], Zm = L[lds_slot<PAD>((N - k) & (N - 1))];
             const uint32_t c = (valid && ((DA && q <= 1) || k <= K)) ? (uint32_t)k * ES : BUF_OOB;
-            bstore<T>(rb, c + o0, 0, {T(0.5) * (Zk.x + Zm.x), T(0.5) * (Zk.y - Zm.y)});
-            bstore<T>(rb, c + o1, 0, {T(0.5) * (Zk.y + Zm.y), T(0.5) * (Zm.x - Zk.x)});
+            cx<T> za = {Zk.x + Zm.x, Zk.y - Zm.y}, zb = {Zk.y + Zm.y, Zm.x - Zk.x};
+            if constexpr (KIND == 2) {   // (a step leaves the half to the prefactor of F_a)
+                za = T(0.5) * za;
+                zb = T(0.5) * zb;
+            }
+            bstore<T>(rb, c + o0, 0, za);
+            bstore<T>(rb, c + o1, 0, zb);
         }
     }
 }
@@ -596,6 +602,7 @@ __global__ void __launch_bounds__(256) k_row_cplx(RowArgs a)
     cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
     if (!IC && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) begin_step(it.ctrl);
     constexpr int TPL = N / 8;
+    constexpr bool WV = N <= 512;   // a line lies in one wavefront
     const int tid = threadIdx.x;
     const int l = tid / TPL, t = tid - l * TPL;
     const int line = blockIdx.x * a.lpw + l;
@@ -647,7 +654,7 @@ __global__ void __launch_bounds__(256) k_row_cplx(RowArgs a)
                 w[0][q] = v[q];
                 w[1][q] = cmul(phs[q], v[q]);
             }
-            fft_lines<T, N, +1, PAD, 2>(w, t, L, 2, 1, tw);
+            fft_lines<T, N, +1, PAD, 2, WV>(w, t, L, 2, 1, tw);
 #pragma unroll
             for (int u = 0; u < 2; u++) {
 #pragma unroll
@@ -657,11 +664,11 @@ __global__ void __launch_bounds__(256) k_row_cplx(RowArgs a)
                     w[u][q] = {m * x, m * y};
                 }
             }
-            fft_lines<T, N, -1, PAD, 2>(w, t, L, 2, 1, tw);
+            fft_lines<T, N, -1, PAD, 2, WV>(w, t, L, 2, 1, tw);
 #pragma unroll
             for (int q = 0; q < 8; q++) v[q] = T(0.5) * (w[0][q] + cmulc(w[1][q], phs[q]));
         } else {
-            fft_line<T, N, +1, PAD>(v, t, L, 1, tw);
+            fft_line<T, N, +1, PAD, WV>(v, t, L, 1, tw);
             // |A|^2 A in real space (CGL)
 #pragma unroll
             for (int q = 0; q < 8; q++) {
@@ -671,7 +678,7 @@ __global__ void __launch_bounds__(256) k_row_cplx(RowArgs a)
             }
         }
     }
-    if (!PS || IC) fft_line<T, N, -1, PAD>(v, t, L, 1, tw);
+    if (!PS || IC) fft_line<T, N, -1, PAD, WV>(v, t, L, 1, tw);
 #pragma unroll
     for (int q = 0; q < 8; q++) bstore<T>(rb, col_off(q), 0, v[q]);
 }
@@ -977,7 +984,8 @@ __global__ void __launch_bounds__(TILE / LPT * N0 / 8) k_axis0(AxisArgs a)
                     const T kl = (g.ndim == 3) ? dk2 * (T)alm : dk1 * (T)alm;
                     const T km = (g.ndim == 3) ? dk1 * (T)a1 : T(0);
                     const T k2 = (dk0 * (T)a0) * (dk0 * (T)a0) + km * km + kl * kl;
-                    const cx<T> F = cmul(nl_pref<T>(it, k2), *slot);
+                    // (a real field's row pass leaves twice the transform)
+                    const cx<T> F = cmul((g.cplx ? T(1) : T(0.5)) * nl_pref<T>(it, k2), *slot);
                     // Fourier-space draws (App. B), or the transformed real-space noise
                     const cx<T> eta = g.rsn ? rnoise[si] : noise_eta<T>(g, it, j0, j1, jlm, (uint32_t)nstep);
                     cx<T> nw = cmul(cur.cf.E, cur.ph) + cmul(cur.cf.wa, F) + cur.cf.G * eta;
@@ -1341,8 +1349,9 @@ __device__ __forceinline__ void axis0r_body(const AxisArgs& a, const int item, c
     const T kl = (g.ndim == 3) ? dk2 * (T)al : dk1 * (T)al;
     const T km = (g.ndim == 3) ? dk1 * (T)a1 : T(0);
     // Fourier prefactor of the nonlinearity, affine in k^2: P0 + P2 k^2 (real
-    // for real fields)
-    const cx<T> P0 = nl_pref<T>(it, T(0)), P2 = nl_pref<T>(it, T(1)) - P0;
+    // for real fields, whose row pass leaves twice the transform)
+    const T half = CC ? T(1) : T(0.5);
+    const cx<T> P0 = half * nl_pref<T>(it, T(0)), P2 = half * nl_pref<T>(it, T(1)) - P0;
     // non-finite detection without branches: x - x is 0 for finite x and NaN
     // for NaN or infinity
     T nfacc = T(0);
