@@ -5,8 +5,7 @@
 // as N1 = RA x 32 and its two factors join the neighbouring passes, so that
 // one array Z in the place of the line buffer is read and written twice per
 // step (CGL 256^3 at 4 realizations: 2.71 -> 1.76 GB and 621 -> 428 us a
-// step; 128^3 at 16: 298 -> 205 us, at 1: 38.4 -> 36.4 us, where the two
-// launches' own latency is what is left).  With
+// step; 128^3 at 16: 298 -> 205 us, at 1: 38.4 -> 31.6 us).  With
 // a1 = 32 p + s and n1 = m + RA r (p, m < RA; s, r < 32)
 //   Z[n0][m][s] = e^{2 pi i s m/N1} sum_p X[32 p + s] e^{2 pi i p m/RA}
 //   x[n0][m + RA r] = sum_s Z[n0][m][s] e^{2 pi i s r/32}
@@ -292,6 +291,208 @@ k_ax01(Part3Args a)
     }
 }
 
+// The step of k_ax01 for launches that leave the chip idle (fewer wavefronts
+// than SIMDs): the same arithmetic in the same order, so the same bits, with
+// the lines of a block taken side by side instead of in turn.  The block's
+// threads take (n0, column) points for the DFTs of RA points over m and leave
+// the kept lines in LDS; each wavefront then takes one line of CPW columns (64
+// = CPW x N0/8 threads) through the axis-0 transform, the update and the
+// inverse without a block barrier; and the points go back by the conjugate
+// DFTs.  us per step against k_ax01's: 128^3 x 1 31.6 / 36.4, 64^3 x 4 17.6 /
+// 21.0; with the chip filled it loses by its 16 to 32-byte segments of the
+// carry: 128^3 x 4 55.6 / 53.6, x 16 225 / 205, 256^3 x 4 458 / 428.
+template <int N0, int RA>
+struct Ax01LdsShape {
+    static constexpr int TPL = N0 / 8, CPW = 64 / TPL, N1 = 32 * RA;
+    static constexpr int TILE = CPW > ZC ? CPW : ZC;
+    // kept lines p of a block: at most 6 of 8 (p = 3, 4 never), 3 of 4 (p = 1 for
+    // s <= 10, p = 2 for s >= 22), both of 2
+    static constexpr int NL = RA == 8 ? 6 : (RA == 4 ? 3 : RA);
+    static constexpr int LSTR = lds_len<N0, 3>() + 4;   // line pitch: columns on different banks
+    static constexpr int TASKS = NL * (TILE / CPW);
+    static constexpr int NW = TASKS < 8 ? TASKS : 8;
+    static constexpr int THREADS = 64 * NW;
+};
+
+template <int N0, int RA>
+__global__ void __launch_bounds__((Ax01LdsShape<N0, RA>::THREADS)) __attribute__((amdgpu_waves_per_eu(4)))
+k_ax01_lds(Part3Args a)
+{
+    typedef float T;
+    typedef Ax01LdsShape<N0, RA> SH;
+    const unsigned lg = xcd_logical(blockIdx.x, gridDim.x);
+    const int item = (int)(lg / (unsigned)a.per_item);
+    const int blk = (int)(lg % (unsigned)a.per_item);
+    const Item it = a.items[item];
+    if (a.sub >= it.steps) return;
+    constexpr int TPL = SH::TPL, CPW = SH::CPW, TILE = SH::TILE, N1 = SH::N1, PAD = 3;
+    constexpr int K0 = (N0 - 1) / 3, KEPT0 = 2 * K0 + 1;
+    constexpr uint32_t ES = sizeof(cx<T>);
+    __shared__ cx<T> lines[SH::NL * TILE * SH::LSTR];
+    const Geo& g = a.g;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tile = blk % a.ntiles, s = blk / a.ntiles;
+    const int keptl = g.kept[2], kept1 = g.kept[1];
+    const uint32_t prow = (uint32_t)g.pitch * ES;   // one row of columns
+    const rsrc_t rz = make_rsrc(it.big, (uint32_t)(N0 * N1) * prow);
+    // stored index of line p, -1 where the 2/3 rule removes it, and the LDS
+    // line it takes
+    auto line_of = [&](int p) { return stored_idx(32 * p + s, N1, kept1, g.kp[1]); };
+    auto slot_of = [](int p) { return RA == 8 ? (p < 3 ? p : p - 2) : (RA == 4 ? (p + 1) / 2 : p); };
+    // e^{-2 pi i s m / N1}, the same in every lane
+    cx<T> wm[RA];
+#pragma unroll
+    for (int m = 1; m < RA; m++) {
+        const cx<T> w = gload<T>(it.tw1, (uint32_t)((s * m) & (N1 - 1)) * ES);
+        wm[m] = {__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(w.x))),
+                 __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(w.y)))};
+    }
+    // point i of the tile: ZC columns of ZN neighbouring n0 (a 128-byte line),
+    // the next n0, the next ZC columns
+    constexpr int POINTS = N0 * TILE;
+    auto point = [&](int i, int& n0, int& c) {
+        c = i % ZC + i / (ZC * N0) * ZC;
+        n0 = i / ZC % N0;
+    };
+    auto zpt = [&](int n0, int c) {
+        return (uint32_t)(n0 / ZN * N1) * (ZN * prow) + z_col(tile * TILE + c) + (uint32_t)(n0 % ZN) * (ZC * ES);
+    };
+    auto zoff = [&](int m) { return (uint32_t)(m * 32 + s) * (ZN * prow); };
+#pragma unroll 2
+    for (int i = tid; i < POINTS; i += SH::THREADS) {
+        int n0, c;
+        point(i, n0, c);
+        const uint32_t z = zpt(n0, c);
+        cx<T> u[RA];
+#pragma unroll
+        for (int m = 0; m < RA; m++) u[m] = bload<T>(rz, z, zoff(m));
+#pragma unroll
+        for (int m = 1; m < RA; m++) u[m] = cmul(u[m], wm[m]);
+        dft<RA, -1>(u);
+        cx<T>* const dst = lines + c * SH::LSTR + lds_slot<PAD>(n0);
+#pragma unroll
+        for (int p = 0; p < RA; p++) {
+            if (RA == 8 && (p == 3 || p == 4)) continue;
+            if (line_of(p) >= 0) dst[slot_of(p) * TILE * SH::LSTR] = u[p];
+        }
+    }
+    __syncthreads();
+
+    const int cw = lane % CPW, t = lane / CPW;   // column within the wavefront's, bins t + q N0/8
+    auto live = [](int q) { return q != 3 && q != 4; };
+    auto stored = [&](int q) {
+        if (q == 3 || q == 4) return false;
+        if (q == 2) return t + 2 * TPL <= K0;
+        if (q == 5) return t + 5 * TPL >= N0 - K0;
+        return true;
+    };
+    // state arrays: row (i0, i1); bins q = 3, 4 hold no stored mode
+    const uint32_t lstride = (uint32_t)kept1 * prow;
+    const rsrc_t rst = make_rsrc(it.prev, (uint32_t)KEPT0 * lstride);
+    const rsrc_t rcoef = make_rsrc(it.coef, it.coef_bytes);
+    LineTw<T, N0> tw;
+    line_tw_load(tw, t, twid<T>(it.tw0));
+    // the row pass has begun the step; the carry holds the next step's noise
+    const uint32_t nn = (uint32_t)*(const SETD_GLOBAL int64_t*)&it.ctrl->step;
+    const bool hp = *(const SETD_GLOBAL int*)&it.ctrl->have_prev >= 2;
+    const cx<T> pref = {T(-1), -(T)it.par0};
+    T nfacc = T(0);
+    // tasks: the columns of line p in groups of CPW
+    constexpr int CG = TILE / CPW;
+#pragma unroll 1
+    for (int k = wave; k < SH::TASKS; k += SH::NW) {
+        const int sl = k / CG;   // LDS line; for RA = 4 line 1 is p = 1 or 2
+        const int p = RA == 8 ? (sl < 3 ? sl : sl + 2) : (RA == 4 && sl == 2 ? 3 : (RA == 4 && sl == 1 && s >= 16 ? 2 : sl));
+        const int i1 = line_of(p);
+        if (i1 < 0) continue;
+        const int c = k % CG * CPW + cw, colm = tile * TILE + c;
+        const bool cv = colm < keptl;
+        const int j1 = 32 * p + s, a1 = sgn_idx(j1, N1);
+        const int jl = fft_pos(colm, g.n[2], keptl, g.kp[2]), al = sgn_idx(jl, g.n[2]);
+        const uint32_t vcol = cv ? (uint32_t)t * lstride + (uint32_t)colm * ES : BUF_OOB;
+        auto voff = [&](int q) { return (q == 2 || q == 5) ? (stored(q) ? vcol : BUF_OOB) : vcol; };
+        auto soff = [&](int q) {
+            return (uint32_t)(q * TPL + (q <= 2 ? 0 : KEPT0 - N0)) * lstride + (uint32_t)i1 * prow;
+        };
+        cx<T>* const L = lines + (sl * TILE + c) * SH::LSTR;
+        cx<T> v[1][8];
+        cx<T> y0[8], eta[8];
+        T4<T> ce[3][2];   // entries of |a0| = t + u N0/8: E, w_a, w_b, G
+#pragma unroll
+        for (int q = 0; q < 8; q++) y0[q] = live(q) ? bload<T>(rst, voff(q), soff(q)) : czero<T>();
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            const int m = t + u * TPL;
+            const uint32_t vo = (cv && m <= K0) ? (uint32_t)coef_key(it, m, a1, al) * (uint32_t)(8 * sizeof(T)) : BUF_OOB;
+            ce[u][0] = bload4<T>(rcoef, vo, 0u);
+            ce[u][1] = bload4<T>(rcoef, vo, 16u);
+        }
+        // noise of bins u and 7 - u from one Philox block, while the loads are in flight
+        const uint32_t S = (uint32_t)g.n[1] * (uint32_t)g.nh_last;
+        const uint32_t rest = (uint32_t)j1 * (uint32_t)g.nh_last + (uint32_t)jl;
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            uint32_t x[4];
+            philox_block(it.seed, (uint32_t)(t + u * TPL) * S + rest, nn, it.r, 0u, x);
+            eta[u] = box_muller_cx(x[0], x[1], T(0));
+            eta[7 - u] = box_muller_cx(x[2], x[3], T(0));
+        }
+#pragma unroll
+        for (int q = 0; q < 8; q++) v[0][q] = L[lds_slot<PAD>(t + q * TPL)];
+        fft_lines<T, N0, -1, PAD, 1, true>(v, t, L, 1, 0, tw);
+        // bin 7 - u of thread t has |a0| = (u + 1) N0/8 - t: entry u of
+        // thread N0/8 - t, or for t = 0 entry u + 1 of its own
+        const int src = (((TPL - t) & (TPL - 1)) * CPW + cw) * 4;
+        auto from = [&](T x) {
+            return __uint_as_float((unsigned)__builtin_amdgcn_ds_bpermute(src, (int)__float_as_uint(x)));
+        };
+        auto update = [&](int q, const T4<T>& e0, const T4<T>& e1) {
+            const bool sv = cv && stored(q);
+            const cx<T> E = {e0.a, e0.b}, wa = {e0.c, e0.d}, wb = {e1.a, e1.b};
+            const cx<T> F = cmul(pref, v[0][q]);
+            // phi_{n+1} = Y_n + w F_n, Y_{n+1} = E phi_{n+1} + w_b F_n + G eta_{n+1}
+            const cx<T> nw = y0[q] + cmul(hp ? wa : wa + wb, F);
+            const cx<T> y = cmul(E, nw) + cmul(wb, F) + e1.c * eta[q];
+            bstore<T>(rst, voff(q), soff(q), y);
+            v[0][q] = sv ? nw : czero<T>();
+            nfacc += (v[0][q].x - v[0][q].x) + (v[0][q].y - v[0][q].y);
+        };
+        v[0][3] = v[0][4] = czero<T>();
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            update(u, ce[u][0], ce[u][1]);
+            const T4<T>&e0 = (t == 0 && u < 2) ? ce[u < 2 ? u + 1 : u][0] : ce[u][0],
+                 &e1 = (t == 0 && u < 2) ? ce[u < 2 ? u + 1 : u][1] : ce[u][1];
+            const T4<T> m0 = {from(e0.a), from(e0.b), from(e0.c), from(e0.d)};
+            const T4<T> m1 = {from(e1.a), from(e1.b), from(e1.c), T(0)};
+            update(7 - u, m0, m1);
+        }
+        fft_lines<T, N0, +1, PAD, 1, true>(v, t, L, 1, 0, tw);
+        exchange_sync<true>();
+#pragma unroll
+        for (int q = 0; q < 8; q++) L[lds_slot<PAD>(t + q * TPL)] = v[0][q];
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int i = tid; i < POINTS; i += SH::THREADS) {
+        int n0, c;
+        point(i, n0, c);
+        const uint32_t z = tile * TILE + c < keptl ? zpt(n0, c) : BUF_OOB;
+        const cx<T>* const src = lines + c * SH::LSTR + lds_slot<PAD>(n0);
+        cx<T> u[RA];
+#pragma unroll
+        for (int p = 0; p < RA; p++) {
+            u[p] = czero<T>();
+            if (RA == 8 && (p == 3 || p == 4)) continue;
+            if (line_of(p) >= 0) u[p] = src[slot_of(p) * TILE * SH::LSTR];
+        }
+        dft<RA, +1>(u);
+#pragma unroll
+        for (int m = 0; m < RA; m++) bstore<T>(rz, z, zoff(m), m ? cmulc(u[m], wm[m]) : u[m]);
+    }
+    if (!(nfacc == nfacc)) atomicOr(&it.ctrl->nonfinite, 1);
+}
+
 // ---------------------------------------------------------------- rows with the inner factor of axis 1
 // Bound by VALU issue (2,540 instructions per wavefront, 135 of 167 us at CGL
 // 256^3 x 4; 0.72 GB moved once).  A row's transform stays within a wavefront,
@@ -414,6 +615,17 @@ static hipError_t launch_ax01(const Geo& g, const Item* items, int nitems, int m
     a.ntiles = g.pitch / TILE;
     a.per_item = a.ntiles * 32;
     a.sub = sub;
+    if constexpr (RA > 1) {
+        // fewer wavefronts than the chip has SIMDs: the lines side by side
+        // (with RA = 1 there is one line a block)
+        if (mode == MODE_STEP && (long)a.per_item * nitems * (TILE * N0 / 8) <= 64L * 1024) {
+            typedef Ax01LdsShape<N0, RA> SH;
+            a.ntiles = g.pitch / SH::TILE;
+            a.per_item = a.ntiles * 32;
+            hipLaunchKernelGGL((k_ax01_lds<N0, RA>), dim3(a.per_item * nitems), dim3(SH::THREADS), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     const dim3 grid(a.per_item * nitems), block(TILE * N0 / 8);
     if (mode == MODE_STEP) hipLaunchKernelGGL((k_ax01<N0, TILE, RA, MODE_STEP>), grid, block, 0, s, a);
     else if (mode == MODE_SYNC) hipLaunchKernelGGL((k_ax01<N0, TILE, RA, MODE_SYNC>), grid, block, 0, s, a);
