@@ -10,8 +10,10 @@
 #include <fstream>
 #include <sstream>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
+#include <thread>
 
 #include "setd_launch.hpp"
 
@@ -837,6 +839,8 @@ void Plan::release()
     graph = nullptr;
     if (cap) (void)hipStreamDestroy(cap);
     cap = nullptr;
+    if (stage) (void)hipHostFree(stage);
+    stage = nullptr;
 }
 
 // Sample series_pos of the window: the stored spectrum of every realization
@@ -1226,51 +1230,122 @@ setd_status Plan::observe(int kind, double* out, size_t cap, size_t* len)
     return f ? fail(SETD_E_NONFINITE, "a realization produced a non-finite value") : SETD_OK;
 }
 
+// fn(i) for i in [0, n) on up to eight host threads (the calling one alone where
+// threads cannot be started); ranges are contiguous and disjoint
+template <typename F>
+static void parallel_ranges(int n, const F& fn)
+{
+    constexpr int MAX = 8;
+    const int want = std::max(1, std::min({MAX, (int)std::thread::hardware_concurrency(), n}));
+    std::thread th[MAX];
+    int started = 1;
+    auto range = [&](int k, int of) {
+        for (int i = (int)((int64_t)n * k / of); i < (int)((int64_t)n * (k + 1) / of); i++) fn(i);
+    };
+    try {
+        for (; started < want; started++) th[started] = std::thread(range, started, want);
+    } catch (...) {
+    }
+    range(0, want);
+    for (int k = started; k < want; k++) range(k, want);   // ranges whose thread did not start
+    for (int k = 1; k < started; k++) th[k].join();
+}
+
+// Output from which a read-out is shared by host threads: us on one thread / on
+// eight at 4 MB (CGL 512^2) 175 / 386, 16 MB (1024^2) 696 / 803, 34 MB (128^3)
+// 2295 / 840, 268 MB (256^3) 29800 / 5730.
+static constexpr size_t PARALLEL_BYTES = (size_t)24 << 20;
+
 // Scatter a stored block (phi or F_{n-1}) of realization r into the unpruned
-// FFT-order layout of the ABI, as interleaved doubles.
+// FFT-order layout of the ABI, as interleaved doubles.  The host side bounds
+// it (the output's pages and the conversion to double): large blocks go
+// through a pinned buffer of the plan, a few planes at a time, and the planes
+// are scattered by several threads.
 setd_status Plan::get_block(size_t off, int r, double* out, size_t cap)
 {
     if (!bound) return fail(SETD_E_STATE, "plan not bound");
     if (r < 0 || r >= R) return fail(SETD_E_INVAL, "realization %d out of range", r);
     if (!out || cap < 2 * nspec) return fail(SETD_E_INVAL, "output needs %zu doubles", 2 * nspec);
-    std::vector<char> host(S * elt);
-    SETD_HIP(hipMemcpyAsync(host.data(), ws + off + (size_t)r * Sb, S * elt, hipMemcpyDeviceToHost, stream));
-    SETD_HIP(hipStreamSynchronize(stream));
-    scatter(host.data(), out);
+    const char* src = ws + off + (size_t)r * Sb;
+    const int planes = d.ndim == 1 ? 1 : g.kept[0];
+    const size_t pb = S * elt / planes;   // bytes of a stored plane
+    if (2 * nspec * sizeof(double) >= PARALLEL_BYTES && !stage && pb <= STAGE_BYTES)
+        if (hipHostMalloc((void**)&stage, STAGE_BYTES, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            stage = nullptr;   // without it the block is copied as a whole
+        }
+    if (!stage || pb > STAGE_BYTES || 2 * nspec * sizeof(double) < PARALLEL_BYTES) {
+        std::unique_ptr<char[]> host(new (std::nothrow) char[S * elt]);
+        if (!host) return fail(SETD_E_NOMEM, "host allocation failed");
+        SETD_HIP(hipMemcpyAsync(host.get(), src, S * elt, hipMemcpyDeviceToHost, stream));
+        SETD_HIP(hipStreamSynchronize(stream));
+        scatter(host.get(), out);
+        return SETD_OK;
+    }
+    const int step = (int)(STAGE_BYTES / pb);
+    for (int i0 = 0; i0 < planes; i0 += step) {
+        const int n = std::min(step, planes - i0);
+        SETD_HIP(hipMemcpyAsync(stage, src + (size_t)i0 * pb, (size_t)n * pb, hipMemcpyDeviceToHost, stream));
+        SETD_HIP(hipStreamSynchronize(stream));
+        parallel_ranges(n, [&](int i) { scatter_plane(stage + (size_t)i * pb, i0 + i, out); });
+    }
+    clear_planes(out);
     return SETD_OK;
 }
 
-// Stored block of one realization (state precision, padded last axis) ->
-// unpruned FFT-order spectrum as interleaved doubles.
-void Plan::scatter(const char* raw, double* out) const
+// Stored plane i0 (state precision, padded last axis) -> its place in the
+// unpruned FFT-order spectrum, removed modes zero.
+void Plan::scatter_plane(const char* raw, int i0, double* out) const
 {
-    std::memset(out, 0, 2 * nspec * sizeof(double));
     const int last = d.ndim - 1;
-    const int k1 = (d.ndim == 3) ? g.kept[1] : 1;
-    for (int i0 = 0; i0 < (d.ndim == 1 ? 1 : g.kept[0]); i0++) {
-        const int j0 = (i0 <= g.kp[0]) ? i0 : i0 + g.n[0] - g.kept[0];
-        for (int i1 = 0; i1 < k1; i1++) {
-            const int j1 = (d.ndim == 3) ? ((i1 <= g.kp[1]) ? i1 : i1 + g.n[1] - g.kept[1]) : 0;
-            for (int c = 0; c < g.kept[last]; c++) {
-                const int jl = g.cplx ? ((c <= g.kp[last]) ? c : c + g.n[last] - g.kept[last]) : c;
-                const size_t src = ((size_t)i0 * k1 + i1) * g.pitch + c;
-                const size_t dst = (d.ndim == 3) ? ((size_t)j0 * g.n[1] + j1) * g.nh_last + jl
-                                                 : (size_t)j0 * g.nh_last + jl;
-                double re, im;
-                if (d.precision == 32) {
-                    const float* f = reinterpret_cast<const float*>(raw) + 2 * src;
-                    re = f[0];
-                    im = f[1];
-                } else {
-                    const double* f = reinterpret_cast<const double*>(raw) + 2 * src;
-                    re = f[0];
-                    im = f[1];
-                }
-                out[2 * dst] = re;
-                out[2 * dst + 1] = im;
+    const int j0 = (d.ndim == 1 || i0 <= g.kp[0]) ? (d.ndim == 1 ? 0 : i0) : i0 + g.n[0] - g.kept[0];
+    const int n1 = (d.ndim == 3) ? g.n[1] : 1, k1 = (d.ndim == 3) ? g.kept[1] : 1;
+    const int kl = g.kept[last], lo = std::min(kl, g.cplx ? g.kp[last] + 1 : kl);   // columns of the low side
+    auto convert = [&](size_t src, double* dst, int n) {
+        if (d.precision == 32) {
+            const float* f = reinterpret_cast<const float*>(raw) + 2 * src;
+            for (int i = 0; i < 2 * n; i++) dst[i] = (double)f[i];
+        } else {
+            std::memcpy(dst, reinterpret_cast<const double*>(raw) + 2 * src, (size_t)2 * n * sizeof(double));
+        }
+    };
+    for (int j1 = 0; j1 < n1; j1++) {
+        double* row = out + 2 * ((size_t)j0 * n1 + j1) * g.nh_last;
+        int i1 = j1;
+        if (d.ndim == 3 && j1 > g.kp[1]) {
+            i1 = j1 - g.n[1] + k1;
+            if (i1 <= g.kp[1]) {
+                std::memset(row, 0, (size_t)2 * g.nh_last * sizeof(double));
+                continue;
             }
         }
+        const size_t s = (size_t)i1 * g.pitch;
+        convert(s, row, lo);
+        std::memset(row + 2 * lo, 0, (size_t)2 * (g.nh_last - kl) * sizeof(double));
+        convert(s + lo, row + 2 * (size_t)(g.nh_last - kl + lo), kl - lo);
     }
+}
+
+// the planes of axis 0 that hold no stored mode
+void Plan::clear_planes(double* out) const
+{
+    if (d.ndim == 1 || g.kept[0] >= g.n[0]) return;
+    const size_t plane = nspec / g.n[0];
+    const int first = g.kp[0] + 1, n = g.n[0] - g.kept[0];
+    auto clear = [&](int i) { std::memset(out + 2 * plane * (size_t)(first + i), 0, 2 * plane * sizeof(double)); };
+    if (2 * nspec * sizeof(double) >= PARALLEL_BYTES) parallel_ranges(n, clear);
+    else for (int i = 0; i < n; i++) clear(i);
+}
+
+// Stored block of one realization -> unpruned FFT-order spectrum.
+void Plan::scatter(const char* raw, double* out) const
+{
+    const int planes = d.ndim == 1 ? 1 : g.kept[0];
+    const size_t pb = S * elt / planes;
+    auto plane = [&](int i) { scatter_plane(raw + (size_t)i * pb, i, out); };
+    if (2 * nspec * sizeof(double) >= PARALLEL_BYTES) parallel_ranges(planes, plane);
+    else for (int i = 0; i < planes; i++) plane(i);
+    clear_planes(out);
 }
 
 setd_status Plan::set_field(int r, const double* in, size_t len)

@@ -131,6 +131,11 @@ struct Plan {
     setd_status observe(int kind, double* out, size_t cap, size_t* len);
     setd_status get_block(size_t off, int r, double* out, size_t cap);
     void scatter(const char* raw, double* out) const;
+    void scatter_plane(const char* raw, int i0, double* out) const;
+    void clear_planes(double* out) const;
+    // pinned buffer of large read-outs, allocated at the first one
+    static constexpr size_t STAGE_BYTES = (size_t)8 << 20;
+    char* stage = nullptr;
     setd_status set_field(int r, const double* in, size_t len);
     setd_status set_step(int64_t step);
     setd_status nonfinite_any(int* flag);

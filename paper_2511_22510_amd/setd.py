@@ -224,9 +224,11 @@ def setd_observe(plan, kind, cap, lib=None, allow_nonfinite=False):
     return out[: ln.value].copy(), st
 
 
-def setd_get_field(plan, r, nspec, lib=None):
+def setd_get_field(plan, r, nspec, lib=None, out=None):
+    """The spectrum of realization r (into out, 2 nspec doubles, if given)."""
     lib = lib or load()
-    out = np.zeros(2 * nspec, dtype=np.float64)
+    if out is None:
+        out = np.empty(2 * nspec, dtype=np.float64)
     _check(lib, lib.setd_get_field(plan, int(r), out.ctypes.data_as(_D), out.size))
     return out.view(np.complex128)
 
@@ -467,7 +469,11 @@ class Plan:
         return setd_get_field(self.h, r, self.nspec, self.lib).reshape(self.spec_shape)
 
     def get_all(self):
-        return np.stack([self.get(r) for r in range(self.R)])
+        # each field straight to its place: a stack of them would copy every one
+        out = np.empty((self.R, 2 * self.nspec), dtype=np.float64)
+        for r in range(self.R):
+            setd_get_field(self.h, r, self.nspec, self.lib, out[r])
+        return out.view(np.complex128).reshape((self.R,) + tuple(self.spec_shape))
 
     def history(self, r=0):
         return setd_get_history(self.h, r, self.nspec, self.lib).reshape(self.spec_shape)

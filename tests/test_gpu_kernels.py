@@ -194,3 +194,32 @@ def test_windows_recorded_by_the_step_kernels(p, M, calls):
     for r in range(min(3, p["realizations"])):
         assert float(np.linalg.norm(g.get(r) - o.get(r))) <= tol * float(np.linalg.norm(o.get(r)))
     g.close()
+
+
+@pytest.mark.parametrize("p", [
+    W.cgl([128, 128, 128], seed=51), W.cgl([64, 64, 64], seed=52, realizations=2),
+    W.cgl([64, 256, 128], seed=53), W.cgl([512, 512], seed=54, precision=64, dealias=0, history_readback=1),
+    W.model_a([256, 128, 128], seed=55, precision=32), W.kpz([1024, 512], seed=56, ic_kind=1, ic_sigma=0.2),
+    W.model_a([64, 512], seed=57, precision=64), W.cgl([1024], seed=58), W.model_a([8, 16], seed=59)])
+def test_read_out_matches_the_device_unpack(p, monkeypatch):
+    """The host read-out (planes scattered by several threads through a pinned
+    buffer for large fields, the whole block on one thread for small ones)
+    gives bitwise what the device unpacks for setd_run_noalloc: every lattice
+    dimension, field type and dealiasing rule, removed modes zero over a
+    buffer that was not.  (setd_run_noalloc steps with the default kernel
+    variants, whose rounding differs from some tuned ones', so the plan does
+    too.)"""
+    S = _setd()
+    monkeypatch.setenv("SETD_AUTOTUNE", "0")
+    g = S.Plan(p)
+    g.step(3)
+    ref = S.run_noalloc(p, 3)
+    import ctypes
+    for r in range(p["realizations"]):
+        buf = np.full(2 * g.nspec + 4, np.nan)
+        S._check(g.lib, g.lib.setd_get_field(g.h, r, buf.ctypes.data_as(S._D), 2 * g.nspec))
+        assert np.isnan(buf[2 * g.nspec:]).all()
+        assert np.array_equal(buf[:2 * g.nspec].view(np.complex128).reshape(ref[r].shape), ref[r])
+    if p.get("history_readback") and p["order"] == 2:
+        assert np.isfinite(g.history(0)).all()
+    g.close()
