@@ -1969,10 +1969,15 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
     const Geo& g = a.g;
     const int tid = threadIdx.x;
     const int l = tid / TPL, t = tid - l * TPL;
-    const int line = blockIdx.x * LPB + l;
+    // (a line of a wavefront or more is the same in all its lanes: its item's
+    // fields and the round keys then stay in scalar registers)
+    const int line0 = blockIdx.x * LPB + l;
+    const int line = TPL >= 64 ? __builtin_amdgcn_readfirstlane(line0) : line0;
     cx<T>* L = reinterpret_cast<cx<T>*>(smem_raw) + (size_t)l * 2 * LL;
     const int ra = 2 * line, rb = 2 * line + 1;
     const bool va = line < a.nlines && ra < a.nitems, vb = line < a.nlines && rb < a.nitems;
+    // both realizations of a line are of one plan or job (the server pads an odd
+    // count): they share its seed, tables and parameters, read from ia
     const Item& ia = a.items[va ? ra : 0];
     const Item& ib = a.items[vb ? rb : (va ? ra : 0)];
     const bool acta = va && a.sub < ia.steps, actb = vb && a.sub < ib.steps;
@@ -1999,8 +2004,8 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
             T z1a = T(0), z2a, z1b = T(0), z2b;
             const uint32_t site = (uint32_t)(t + q * M);
             if (va) normal_pair(ia.seed, site, 0u, ia.r, 1u, z1a, z2a);
-            if (vb) normal_pair(ib.seed, site, 0u, ib.r, 1u, z1b, z2b);
-            v[q] = {(T)ia.ic_sigma * z1a, (T)ib.ic_sigma * z1b};
+            if (vb) normal_pair(ia.seed, site, 0u, ib.r, 1u, z1b, z2b);
+            v[q] = {(T)ia.ic_sigma * z1a, (T)ia.ic_sigma * z1b};
         }
         fft_line<T, N, -1, PAD>(v, t, L, 1, tw);
         __syncthreads();
@@ -2035,7 +2040,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
     // holds the state, F_{n-1} and G times 1/N (a power of two, so exactly):
     // the inverse transform then gives the field itself.
     cx<T> fa[QS], fb[QS];
-    Coef<T> ca[QS], cb[QS];
+    Coef<T> cf[QS];
     const cx<T>* phia0 = reinterpret_cast<const cx<T>*>(ia.phi);
     const cx<T>* phib0 = reinterpret_cast<const cx<T>*>(ib.phi);
     const cx<T>* preva = reinterpret_cast<const cx<T>*>(ia.prev);
@@ -2046,30 +2051,29 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
 #pragma unroll
     for (int q = 0; q < QS; q++) {
         pa[q] = pb[q] = fa[q] = fb[q] = czero<T>();
-        ca[q] = cb[q] = Coef<T>{czero<T>(), czero<T>(), czero<T>(), T(0)};
+        cf[q] = Coef<T>{czero<T>(), czero<T>(), czero<T>(), T(0)};
         if (!stored(q)) continue;
         const int m = mode_of(q);
+        if (va) cf[q] = load_coef_t<T, false>(ia.coef, m);   // real fields: real tables, keyed by |a|
+        cf[q].G *= inv;
         // a realization that does not step in this launch is no partner: its
         // channel stays zero, as for the missing partner of an odd count
         if (acta) {
             pa[q] = inv * phia0[m];
             if (o2 && hpa) fa[q] = inv * preva[m];
-            ca[q] = load_coef_t<T, false>(ia.coef, m);   // real fields: real tables, keyed by |a|
-            ca[q].G *= inv;
         }
         if (actb) {
             pb[q] = inv * phib0[m];
             if (o2 && hpb) fb[q] = inv * prevb[m];
-            cb[q] = load_coef_t<T, false>(ib.coef, m);
-            cb[q].G *= inv;
         }
         if (m == 0 || 2 * m == N) {
             pa[q].y = T(0);
             pb[q].y = T(0);
         }
     }
-    const T dka = (T)ia.dk[0], dkb = (T)ib.dk[0];
-    const cx<T> pra = nl_pref<T>(ia, T(0)), prb = nl_pref<T>(ib, T(0));
+    const T dk = (T)ia.dk[0];
+    const T pr = nl_pref<T>(ia, T(0)).x;
+    const uint64_t seed = ia.seed;
     // real-space noise of step s: site x = t + qM of both realizations from
     // Philox blocks (x mod N/4, n, r, 3): block t + hM gives sites q = h,
     // h + 2 (half 0) and h + 4, h + 6 (half 1)
@@ -2082,7 +2086,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
             uint32_t x[4];
             T z1, z2, z3, z4;
             if (acta) {
-                philox_block(ia.seed, P, (uint32_t)(stepa + s), ia.r, 3u, x);
+                philox_block(seed, P, (uint32_t)(stepa + s), ia.r, 3u, x);
                 box_muller32(x[0], x[1], z1, z2);
                 box_muller32(x[2], x[3], z3, z4);
                 e[h].x = z1;
@@ -2091,7 +2095,7 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 e[h + 6].x = z4;
             }
             if (actb) {
-                philox_block(ib.seed, P, (uint32_t)(stepb + s), ib.r, 3u, x);
+                philox_block(seed, P, (uint32_t)(stepb + s), ib.r, 3u, x);
                 box_muller32(x[0], x[1], z1, z2);
                 box_muller32(x[2], x[3], z3, z4);
                 e[h].y = z1;
@@ -2117,8 +2121,8 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 if constexpr (KIND == 1) {
                     // h' = i k h, the Nyquist derivative dropped
                     const T kk = (2 * m == N) ? T(0) : (T)m;
-                    A = {-kk * dka * pa[q].y, kk * dka * pa[q].x};
-                    B = {-kk * dkb * pb[q].y, kk * dkb * pb[q].x};
+                    A = {-kk * dk * pa[q].y, kk * dk * pa[q].x};
+                    B = {-kk * dk * pb[q].y, kk * dk * pb[q].x};
                 }
                 L[lds_slot<PAD>(m)] = A;
                 L[LL + lds_slot<PAD>(m)] = B;
@@ -2229,12 +2233,11 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                 // (twice the two spectra: the half is in the factors below)
                 const cx<T> wa = {Zk.x + Zm.x, Zk.y - Zm.y};
                 const cx<T> wb = {Zk.y + Zm.y, Zm.x - Zk.x};
-                const T k2a = (dka * (T)k) * (dka * (T)k), k2b = (dkb * (T)k) * (dkb * (T)k);
                 // Model B: -u k^2; the others a constant
-                const T sa = (ia.nl == NL_PHI3_CONS) ? -(T)ia.par0 * k2a : pra.x;
-                const T sb = (ib.nl == NL_PHI3_CONS) ? -(T)ib.par0 * k2b : prb.x;
-                F1[q] = (T(0.5) * inv * sa) * wa;
-                F2[q] = (T(0.5) * inv * sb) * wb;
+                const T kq = dk * (T)k;
+                const T sc = T(0.5) * inv * ((ia.nl == NL_PHI3_CONS) ? -(T)ia.par0 * (kq * kq) : pr);
+                F1[q] = sc * wa;
+                F2[q] = sc * wb;
             }
         }
         cx<T> ea[QS], eb[QS];
@@ -2254,8 +2257,8 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
             for (int h = 0; h < 2; h++) {
                 uint32_t xa[4], xb[4];
                 const uint32_t P = (uint32_t)(t + h * M);
-                if (acta) philox_block(ia.seed, P, (uint32_t)(stepa + s), ia.r, 0u, xa);
-                if (actb) philox_block(ib.seed, P, (uint32_t)(stepb + s), ib.r, 0u, xb);
+                if (acta) philox_block(seed, P, (uint32_t)(stepa + s), ia.r, 0u, xa);
+                if (actb) philox_block(seed, P, (uint32_t)(stepb + s), ib.r, 0u, xb);
 #pragma unroll
                 for (int u = 0; u < 2; u++) {
                     const int q = h + 2 * u;
@@ -2277,11 +2280,11 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
                     ns.half = 0u;
                     ns.kind = 1;
                     if (acta) {
-                        philox_block(ia.seed, ns.P, (uint32_t)(stepa + s), ia.r, 0u, xa);
+                        philox_block(seed, ns.P, (uint32_t)(stepa + s), ia.r, 0u, xa);
                         ea[4] = eta_of<T>(xa, ns);
                     }
                     if (actb) {
-                        philox_block(ib.seed, ns.P, (uint32_t)(stepb + s), ib.r, 0u, xb);
+                        philox_block(seed, ns.P, (uint32_t)(stepb + s), ib.r, 0u, xb);
                         eb[4] = eta_of<T>(xb, ns);
                     }
                 }
@@ -2293,11 +2296,11 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
         for (int q = 0; q < QS; q++) {
             if (!stored(q)) continue;
             const int m = mode_of(q);
-            cx<T> na = ca[q].E.x * pa[q] + ca[q].wa.x * F1[q] + ca[q].G * ea[q];
-            cx<T> nb = cb[q].E.x * pb[q] + cb[q].wa.x * F2[q] + cb[q].G * eb[q];
+            cx<T> na = cf[q].E.x * pa[q] + cf[q].wa.x * F1[q] + cf[q].G * ea[q];
+            cx<T> nb = cf[q].E.x * pb[q] + cf[q].wa.x * F2[q] + cf[q].G * eb[q];
             if (o2) {
-                na = na + ca[q].wb.x * (upa ? fa[q] : F1[q]);
-                nb = nb + cb[q].wb.x * (upb ? fb[q] : F2[q]);
+                na = na + cf[q].wb.x * (upa ? fa[q] : F1[q]);
+                nb = nb + cf[q].wb.x * (upb ? fb[q] : F2[q]);
                 fa[q] = F1[q];
                 fb[q] = F2[q];
             }
@@ -2368,7 +2371,8 @@ __global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
     const Geo& g = a.g;
     const int tid = threadIdx.x;
     const int l = tid / TPL, t = tid - l * TPL;
-    const int line = blockIdx.x * LPB + l;
+    const int line0 = blockIdx.x * LPB + l;
+    const int line = TPL >= 64 ? __builtin_amdgcn_readfirstlane(line0) : line0;   // as in k_line1d_real
     // one line of LDS per line, two where a second line shares the stages
     // (the launcher sizes the allocation the same way)
     constexpr int LSTR = (RS || PS) ? 2 * LL : LL;
