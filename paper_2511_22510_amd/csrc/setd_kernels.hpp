@@ -1956,13 +1956,17 @@ __device__ __forceinline__ void line1d_tw(Line1dTw<T, N, KIND>& tw, int t, const
 // per realization with its own noise, table and step.  KIND 0: phi^3 (Model A,
 // and Model B with its k^2 in the prefactor), 1: KPZ ((lambda/2) h'^2 from the
 // line of h + i h' per realization pair), 2: no nonlinearity.
+// Threads of a block: a line of two wavefronts (N = 1024) has block barriers and
+// takes a block of its own, so that no other line waits at them.
+constexpr int line1d_threads(int N) { return N / 8 > 64 ? N / 8 : 256; }
+
 template <typename T, int N, int PAD, int DM, int KIND, bool RS>
-__global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
+__global__ void __launch_bounds__(line1d_threads(N)) k_line1d_real(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
-    constexpr int LPB = 256 / TPL;
+    constexpr int LPB = line1d_threads(N) / TPL;
     constexpr int LL = lds_len<N, PAD>();
     constexpr int QS = DA ? 3 : (PS ? 4 : 5);    // register slots of stored modes
     constexpr bool WV = N <= 512;                // a line lies in one wavefront
@@ -2360,12 +2364,12 @@ __global__ void __launch_bounds__(256) k_line1d_real(Line1dArgs a)
 // of phi (FFT order).  KIND 0: CGL, F = -(1 + i beta) FFT[|phi|^2 phi];
 // 1: no nonlinearity.  The noise block t + qM (q < 4) serves bins q and 7 - q.
 template <typename T, int N, int PAD, int DM, int KIND, bool RS>
-__global__ void __launch_bounds__(256) k_line1d_cplx(Line1dArgs a)
+__global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
-    constexpr int LPB = 256 / TPL;
+    constexpr int LPB = line1d_threads(N) / TPL;
     constexpr bool WV = N <= 512;   // a line lies in one wavefront
     constexpr int LL = lds_len<N, PAD>();
     const Geo& g = a.g;

@@ -449,7 +449,7 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
 {
     // FP32 lines pad LDS by one slot per 8 (fewer bank conflicts in the
     // exchanges); FP64 lines would exceed 64 KiB of LDS with it
-    constexpr int TPL = N / 8, LPB = 256 / TPL, PAD = sizeof(T) == 4 ? 3 : 0;
+    constexpr int TPL = N / 8, BT = line1d_threads(N), LPB = BT / TPL, PAD = sizeof(T) == 4 ? 3 : 0;
     constexpr int LL = lds_len<N, PAD>();
     Line1dArgs a;
     a.g = g;
@@ -463,16 +463,16 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
         a.nlines = nitems;
         const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
         const size_t lds = (size_t)LPB * ((RS || DM == 2) ? 2 : 1) * LL * sizeof(cx<T>);
-        if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS>), grid, dim3(256), lds, s, a);
-        else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS>), grid, dim3(256), lds, s, a);
+        if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS>), grid, dim3(BT), lds, s, a);
+        else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS>), grid, dim3(BT), lds, s, a);
         return hipGetLastError();
     }
     a.nlines = (nitems + 1) / 2;
     const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
     const size_t lds = (size_t)LPB * 2 * LL * sizeof(cx<T>);
-    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS>), grid, dim3(256), lds, s, a);
-    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS>), grid, dim3(256), lds, s, a);
-    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS>), grid, dim3(256), lds, s, a);
+    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS>), grid, dim3(BT), lds, s, a);
+    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS>), grid, dim3(BT), lds, s, a);
+    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS>), grid, dim3(BT), lds, s, a);
     return hipGetLastError();
 }
 
