@@ -1958,20 +1958,25 @@ __device__ __forceinline__ void line1d_tw(Line1dTw<T, N, KIND>& tw, int t, const
 // line of h + i h' per realization pair), 2: no nonlinearity.
 // Threads of a block: a line of two wavefronts (N = 1024) has block barriers and
 // takes a block of its own, so that no other line waits at them.
+// A lone wavefront on its SIMD is bound by its own instructions, a third of them
+// the noise: NW draws it in a second wavefront, one step ahead through LDS, with
+// one block barrier a step (the same values, so the same bits).
 constexpr int line1d_threads(int N) { return N / 8 > 64 ? N / 8 : 256; }
 
-template <typename T, int N, int PAD, int DM, int KIND, bool RS>
-__global__ void __launch_bounds__(line1d_threads(N)) k_line1d_real(Line1dArgs a)
+template <typename T, int N, int PAD, int DM, int KIND, bool RS, bool NW>
+__global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
-    constexpr int LPB = line1d_threads(N) / TPL;
+    constexpr int CT = NW ? 64 : line1d_threads(N);   // threads that step lines
+    constexpr int LPB = CT / TPL;
     constexpr int LL = lds_len<N, PAD>();
     constexpr int QS = DA ? 3 : (PS ? 4 : 5);    // register slots of stored modes
     constexpr bool WV = N <= 512;                // a line lies in one wavefront
     const Geo& g = a.g;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & (CT - 1);   // (NW: lane of either wavefront)
+    const bool drawer = NW && threadIdx.x >= CT;
     const int l = tid / TPL, t = tid - l * TPL;
     // (a line of a wavefront or more is the same in all its lanes: its item's
     // fields and the round keys then stay in scalar registers)
@@ -2111,9 +2116,73 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_real(Line1dArgs a)
     };
     (void)site_noise;
     const T rsq = (T)(1.0 / sqrt((double)N));
+    auto fourier_noise = [&](cx<T> (&ea)[QS], cx<T> (&eb)[QS], int s) {
+        // Fourier draws: block t serves modes t and t + 2M, block t + M
+        // serves t + M and t + 3M, block 2M the Nyquist mode (thread 0)
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            uint32_t xa[4], xb[4];
+            const uint32_t P = (uint32_t)(t + h * M);
+            if (acta) philox_block(seed, P, (uint32_t)(stepa + s), ia.r, 0u, xa);
+            if (actb) philox_block(seed, P, (uint32_t)(stepb + s), ib.r, 0u, xb);
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                const int q = h + 2 * u;
+                if (q >= QS) continue;
+                NoiseSlot ns;
+                ns.P = P;
+                ns.half = (uint32_t)u;
+                ns.kind = (q == 0 && t == 0) ? 1 : 0;
+                ea[q] = acta ? eta_of<T>(xa, ns) : czero<T>();
+                eb[q] = actb ? eta_of<T>(xb, ns) : czero<T>();
+            }
+        }
+        if constexpr (DM == 0) {
+            ea[4] = eb[4] = czero<T>();
+            if (t == 0) {
+                uint32_t xa[4], xb[4];
+                NoiseSlot ns;
+                ns.P = (uint32_t)(2 * M);
+                ns.half = 0u;
+                ns.kind = 1;
+                if (acta) {
+                    philox_block(seed, ns.P, (uint32_t)(stepa + s), ia.r, 0u, xa);
+                    ea[4] = eta_of<T>(xa, ns);
+                }
+                if (actb) {
+                    philox_block(seed, ns.P, (uint32_t)(stepb + s), ib.r, 0u, xb);
+                    eb[4] = eta_of<T>(xb, ns);
+                }
+            }
+        }
+    };
+    // NW: the second wavefront's draws of steps s and s + 1
+    __shared__ cx<T> eta[NW ? 4 * QS : 1][64];
+    auto leave_noise = [&](int s) {
+        cx<T> ea[QS], eb[QS];
+        fourier_noise(ea, eb, s);
+#pragma unroll
+        for (int q = 0; q < QS; q++) {
+            eta[((s & 1) * 2 + 0) * QS + q][tid] = ea[q];
+            eta[((s & 1) * 2 + 1) * QS + q][tid] = eb[q];
+        }
+    };
+    (void)fourier_noise;
+    (void)leave_noise;
+    if constexpr (NW) {
+        if (drawer) {
+#pragma unroll 1
+            for (int s = 0; s <= a.nsteps; s++) {
+                if (s < a.nsteps) leave_noise(s);
+                __syncthreads();
+            }
+        } else {
+            __syncthreads();
+        }
+    }
 
 #pragma unroll 1
-    for (int s = 0; s < a.nsteps; s++) {
+    for (int s = 0; s < (drawer ? 0 : a.nsteps); s++) {
         if constexpr (KIND != 2) {
             // pack the two half spectra (KPZ: of h and h' per realization)
             exchange_sync<WV>();
@@ -2255,43 +2324,14 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_real(Line1dArgs a)
                 eb[q] = {rsq * T(0.5) * (Ek.y + Em.y), rsq * T(0.5) * (Em.x - Ek.x)};
             }
         } else {
-            // Fourier draws: block t serves modes t and t + 2M, block t + M
-            // serves t + M and t + 3M, block 2M the Nyquist mode (thread 0)
+            if constexpr (NW) {
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                uint32_t xa[4], xb[4];
-                const uint32_t P = (uint32_t)(t + h * M);
-                if (acta) philox_block(seed, P, (uint32_t)(stepa + s), ia.r, 0u, xa);
-                if (actb) philox_block(seed, P, (uint32_t)(stepb + s), ib.r, 0u, xb);
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const int q = h + 2 * u;
-                    if (q >= QS) continue;
-                    NoiseSlot ns;
-                    ns.P = P;
-                    ns.half = (uint32_t)u;
-                    ns.kind = (q == 0 && t == 0) ? 1 : 0;
-                    ea[q] = acta ? eta_of<T>(xa, ns) : czero<T>();
-                    eb[q] = actb ? eta_of<T>(xb, ns) : czero<T>();
+                for (int q = 0; q < QS; q++) {
+                    ea[q] = eta[((s & 1) * 2 + 0) * QS + q][tid];
+                    eb[q] = eta[((s & 1) * 2 + 1) * QS + q][tid];
                 }
-            }
-            if constexpr (DM == 0) {
-                ea[4] = eb[4] = czero<T>();
-                if (t == 0) {
-                    uint32_t xa[4], xb[4];
-                    NoiseSlot ns;
-                    ns.P = (uint32_t)(2 * M);
-                    ns.half = 0u;
-                    ns.kind = 1;
-                    if (acta) {
-                        philox_block(seed, ns.P, (uint32_t)(stepa + s), ia.r, 0u, xa);
-                        ea[4] = eta_of<T>(xa, ns);
-                    }
-                    if (actb) {
-                        philox_block(seed, ns.P, (uint32_t)(stepb + s), ib.r, 0u, xb);
-                        eb[4] = eta_of<T>(xb, ns);
-                    }
-                }
+            } else {
+                fourier_noise(ea, eb, s);
             }
         }
         // Eq. SETD1 / SETD2 (the first step of a fresh state takes F_{n-1} = F_n)
@@ -2320,6 +2360,11 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_real(Line1dArgs a)
                 if (actb) reinterpret_cast<cx<T>*>((char*)ib.phi + o)[m] = T(N) * nb;
             }
         }
+        if constexpr (NW) __syncthreads();   // the draws of step s are read, those of s + 1 written
+    }
+    if (drawer) {
+        __syncthreads();   // the one before the counters advance
+        return;
     }
     cx<T>* phia = reinterpret_cast<cx<T>*>(ia.phi);
     cx<T>* phib = reinterpret_cast<cx<T>*>(ib.phi);

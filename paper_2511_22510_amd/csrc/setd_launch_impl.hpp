@@ -468,11 +468,27 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
         return hipGetLastError();
     }
     a.nlines = (nitems + 1) / 2;
+    // Launches of at most a wavefront per SIMD (1024) leave the noise to a second
+    // wavefront per line wavefront.  256 sites, FP32, us per step, one wavefront
+    // against two: 256 line wavefronts 2.85 / 1.72, 1024 2.92 / 2.07, 2048 3.24 /
+    // 4.24 (the registers then hold both kinds no more), 4096 6.17 / 7.15; FP64
+    // 256: 6.20 / 2.76, 1024: 6.22 / 4.44.
+    if constexpr (!RS && N <= 512) {
+        if (mode == MODE_STEP && (long)a.nlines * TPL <= 1024L * 64) {
+            constexpr int LPW = 64 / TPL;
+            const dim3 grid((unsigned)((a.nlines + LPW - 1) / LPW));
+            const size_t lds = (size_t)LPW * 2 * LL * sizeof(cx<T>);
+            if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS, true>), grid, dim3(128), lds, s, a);
+            else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS, true>), grid, dim3(128), lds, s, a);
+            else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS, true>), grid, dim3(128), lds, s, a);
+            return hipGetLastError();
+        }
+    }
     const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
     const size_t lds = (size_t)LPB * 2 * LL * sizeof(cx<T>);
-    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS>), grid, dim3(BT), lds, s, a);
-    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS>), grid, dim3(BT), lds, s, a);
-    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS>), grid, dim3(BT), lds, s, a);
+    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS, false>), grid, dim3(BT), lds, s, a);
+    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS, false>), grid, dim3(BT), lds, s, a);
+    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS, false>), grid, dim3(BT), lds, s, a);
     return hipGetLastError();
 }
 

@@ -223,3 +223,22 @@ def test_read_out_matches_the_device_unpack(p, monkeypatch):
     if p.get("history_readback") and p["order"] == 2:
         assert np.isfinite(g.history(0)).all()
     g.close()
+
+
+@pytest.mark.parametrize("n,large,model,order,precision,dealias", [
+    (64, 16390, "model_a", 1, 32, 1), (64, 16390, "kpz", 2, 32, 2), (512, 2054, "model_b", 2, 32, 0),
+    (512, 2054, "kpz", 2, 64, 1), (128, 8198, "model_a", 2, 64, 2)])
+def test_lines_draw_in_a_second_wavefront_alike(n, large, model, order, precision, dealias):
+    """A line's steps have the same bits whether its noise is drawn by a
+    wavefront of its own (launches of at most 1024 line wavefronts) or not."""
+    out = []
+    for R in (4, large):
+        pl = _setd().Plan(getattr(W, model)([n], seed=9, realizations=R, precision=precision, order=order,
+                                            dealias=dealias, ic_kind=1, ic_sigma=0.2))
+        pl.step(1)
+        pl.step(2)
+        pl.step(37)
+        out.append([pl.get(r) for r in range(4)])
+        pl.close()
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
