@@ -535,11 +535,15 @@ static hipError_t launch_spectrum_m(const SpecArgs& a0, hipStream_t s)
     constexpr int PAD = 3;
     constexpr int tpl = M / 8;
     const int lpb = tpl >= 256 ? 1 : 256 / tpl;
-    // as many realizations per block as leave about four blocks per CU, at
-    // most 64 (the registers sum them before the atomics)
+    // As many realizations per block (at most 64; the registers sum them before
+    // the atomics) as leave one round of blocks: the FP32 kernel's registers hold
+    // two per CU, 512.  us per spectrum read, at 256 / 512 / 1024 blocks: 256 sites
+    // x 1024 realizations x 256 samples 394 / 296 / 309, 512 x 301 x 256 413 / 351 /
+    // 367, 64^2 x 16 x 64 88 / 90 / 100; windows of few lines do not change.
     const int lines = (a.total + lpb - 1) / lpb;
-    a.rper = (int)(((long)lines * a.nitems) / 1024);
-    a.rper = a.rper < 1 ? 1 : (a.rper > 64 ? 64 : a.rper);
+    const int groups = lines < 512 ? 512 / lines : 1;
+    a.rper = (a.nitems + groups - 1) / groups;
+    a.rper = a.rper > 64 ? 64 : a.rper;
     dim3 grid(lines, (a.nitems + a.rper - 1) / a.rper);
     const size_t lds = (size_t)lpb * 2 * lds_len<M, PAD>() * 2 * sizeof(T);
     hipLaunchKernelGGL((k_spectrum<T, M, PAD>), grid, dim3(lpb * tpl), lds, s, a);
