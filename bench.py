@@ -39,7 +39,7 @@ VALU_FILE = os.path.join(ROOT, "profiles", "valu_model_b_512.txt")
 # wave-instructions/s (x 64 lanes x 2 flops = 78.6 TFLOP/s, half the packed
 # FP32 vector peak of 157.3)
 PEAK_VALU_WINST = 256 * 4 / 4 * 2.4e9
-KERNEL_SOURCES = ["setd_device.hpp", "setd_kernels.hpp", "setd_launch_impl.hpp", "setd_types.hpp"]
+KERNEL_SOURCES = ["setd_device.hpp", "setd_kernels.hpp", "setd_launch_impl.hpp", "setd_part3.hip", "setd_types.hpp"]
 # kernel variants the autotuner chose for the workloads timed here on MI355X
 TUNED_TABLE = os.path.join(ROOT, "paper_2511_22510_amd", "tuned_mi355x.txt")
 
