@@ -1956,6 +1956,9 @@ __device__ __forceinline__ void line1d_tw(Line1dTw<T, N, KIND>& tw, int t, const
 // per realization with its own noise, table and step.  KIND 0: phi^3 (Model A,
 // and Model B with its k^2 in the prefactor), 1: KPZ ((lambda/2) h'^2 from the
 // line of h + i h' per realization pair), 2: no nonlinearity.
+// Bound by VALU issue where the lines fill the chip.  us per step, before the
+// exchanges ordered by wavefront, the scaled state and the tables shared by the
+// pair / now: Model A N = 256 x 16384 8.9 / 6.2-6.7, KPZ N = 1024 x 4096 11.2 / 9.6.
 // Threads of a block: a line of two wavefronts (N = 1024) has block barriers and
 // takes a block of its own, so that no other line waits at them.
 // A lone wavefront on its SIMD is bound by its own instructions, a third of them
