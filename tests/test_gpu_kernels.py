@@ -242,3 +242,23 @@ def test_lines_draw_in_a_second_wavefront_alike(n, large, model, order, precisio
         pl.close()
     for a, b in zip(*out):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,R", [((256, 512), 11), ((512, 512), 8)])
+def test_late_blocks_of_a_launch_take_the_same_step(n, R):
+    """The row pass begins a step and the axis-0 pass only reads it: whichever
+    blocks of a launch larger than the chip run last, every realization takes
+    its first SETD2 step as the oracle does (a few eps per transform stage and
+    step) and with the same bits each time."""
+    S = _setd()
+    p = W.cgl(list(n), seed=77, realizations=R, precision=64)
+    g, o = S.Plan(p), O.Sim(p)
+    assert _trajectory_error(g, o, R, (1, 2)) <= 1e-12
+    a = g.get_all()
+    g.close()
+    for _ in range(3):
+        g = S.Plan(p)
+        g.step(1)
+        g.step(2)
+        assert np.array_equal(g.get_all(), a)
+        g.close()
