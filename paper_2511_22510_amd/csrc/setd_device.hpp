@@ -234,7 +234,7 @@ struct FftPlan {
 // LDS slot of element e with one pad slot after every 2^PAD elements
 // (PAD = 0: no padding).  Spreads the strided Stockham writes over the banks.
 template <int PAD>
-__device__ __forceinline__ int lds_slot(int e)
+__host__ __device__ __forceinline__ constexpr int lds_slot(int e)
 {
     if constexpr (PAD > 0) return e + (e >> PAD);
     else return e;

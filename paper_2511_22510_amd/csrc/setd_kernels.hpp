@@ -1124,6 +1124,16 @@ constexpr int axis0r_waves()
     return blocks * w / 4 > 1 ? blocks * w / 4 : 1;
 }
 
+// LDS of a block of k_axis0r, in values: the lines of the tile and, for the
+// carry of a one-column tile of a real field, a second line (HERM_CARRY below).
+// The Hermitian column exchanges its state in its own slots and its carry
+// HERM_CARRY values further on: in the slots of column 1, or past the line
+// where the tile has one column.
+template <int N0, int TILE, int PAD>
+constexpr int herm_carry() { return TILE > 1 ? 1 : lds_len<N0, PAD>(); }
+template <int N0, int TILE, int PAD, int KIND, bool LEAN>
+constexpr int axis0r_lds() { return (TILE == 1 && LEAN && KIND != 2 ? 2 : TILE) * lds_len<N0, PAD>(); }
+
 // The body runs one column tile (blk) of one item with TILE * N0 / 8 threads
 // (tid) and the LDS at byte lds_off; herm_sync says whether the block holding
 // these threads also holds tile 0 of a 2D lattice (its Hermitian column needs
@@ -1430,6 +1440,11 @@ __device__ __forceinline__ void axis0r_body(const AxisArgs& a, const int item, c
     // (q <= 2) independent; row 0 is self-conjugate.  LDS is free between the
     // barrier above and the one that opens the inverse transform.
     if constexpr (!CC) {
+        constexpr int HERM_CARRY = herm_carry<N0, TILE, PAD>();
+        static_assert(HERM_CARRY % TILE != 0 || HERM_CARRY >= TILE * lds_len<N0, PAD>(),
+                      "a carry in the state slot of another row");
+        static_assert(!LEAN || lds_slot<PAD>(N0 - 1) * TILE + HERM_CARRY < axis0r_lds<N0, TILE, PAD, KIND, LEAN>(),
+                      "a carry past the LDS of the block");
         if (g.ndim == 2 && herm_sync) {
             if (tile == 0 && c0 == 0) {
 #pragma unroll
@@ -1437,7 +1452,7 @@ __device__ __forceinline__ void axis0r_body(const AxisArgs& a, const int item, c
                     if (!stored(q)) continue;
                     const int sl = lds_slot<PAD>(t + q * TPL) * TILE;
                     lds[sl] = v[0][q];
-                    if constexpr (LEAN) lds[sl + 1] = ysv[q];
+                    if constexpr (LEAN) lds[sl + HERM_CARRY] = ysv[q];
                 }
             }
             __syncthreads();
@@ -1449,7 +1464,7 @@ __device__ __forceinline__ void axis0r_body(const AxisArgs& a, const int item, c
                     const cx<T> pv = lds[sl];
                     v[0][q] = {pv.x, -pv.y};
                     if constexpr (LEAN) {
-                        const cx<T> py = lds[sl + 1];
+                        const cx<T> py = lds[sl + HERM_CARRY];
                         bstore<T>(rprev, voff(q), soff(q), {py.x, -py.y});
                     } else {
                         bstore<T>(rphi, voff(q), soff(q), v[0][q]);

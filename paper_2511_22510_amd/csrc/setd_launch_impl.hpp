@@ -236,7 +236,8 @@ static hipError_t launch_axis0r(const Geo& g, const Item* items, int nitems, int
     a.sub = sub;
     dim3 grid(a.per_item * nitems);
     dim3 block(TILE * (N / 8));
-    size_t lds = (size_t)TILE * lds_len<N, PAD>() * 2 * sizeof(T);
+    const int len = (lean && !g.cplx) ? axis0r_lds<N, TILE, PAD, 0, true>() : TILE * lds_len<N, PAD>();
+    size_t lds = (size_t)len * 2 * sizeof(T);
     // 3D lattices key their coefficients by |a|: the block stages the entries
     // of |a0| <= K0 for its columns in LDS when they fit in 64 KiB
     const size_t tab = (size_t)(g.kp[0] + 1) * TILE * (g.cplx ? 8 : 4) * sizeof(T);

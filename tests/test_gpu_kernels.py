@@ -262,3 +262,20 @@ def test_late_blocks_of_a_launch_take_the_same_step(n, R):
         g.step(2)
         assert np.array_equal(g.get_all(), a)
         g.close()
+
+
+@pytest.mark.parametrize("variant", ["0,12,0", "1,12,0", "1,15,0"])
+@pytest.mark.parametrize("kind", ["model_a", "model_b", "kpz"])
+def test_one_column_axis_0_tiles(kind, variant, monkeypatch):
+    """FP64 lines of 1024 rows have axis-0 tiles of a single column (the
+    quarter-width variants), where the Hermitian column's state and SETD2 carry
+    lie in lines of their own in LDS: the trajectory follows the oracle to the
+    FP64 bar, with the carry alone and with both arrays stored."""
+    S = _setd()
+    monkeypatch.setenv("SETD_VARIANT", variant)
+    for history in (0, 1):
+        p = getattr(W, kind)([1024, 32], seed=31, realizations=2, precision=64, order=2, ic_kind=1, ic_sigma=0.2,
+                             history_readback=history)
+        g, o = S.Plan(p), O.Sim(p)
+        assert _trajectory_error(g, o, 2, (1, 1, 4, 6)) <= 1e-10
+        g.close()
