@@ -202,9 +202,12 @@ typedef struct {
     size_t spectral_len;      /* complex values per realization crossing the ABI   */
     size_t kept_modes;        /* stored (non-dealiased) modes per realization      */
     int nbins;                /* shell bins of the S(k) and two-time observables   */
-    int passes_per_step;      /* kernel launches per time step (a plan whose
-                                 step takes fewer passes than the general 2D or
-                                 3D path says so once bound)                      */
+    int passes_per_step;      /* kernel launches per time step.  This and the two
+                                 byte counts describe the general 2D or 3D path
+                                 until the plan is bound, the path it steps with
+                                 from then on (a 2D lattice of 32 or 64 points
+                                 per axis takes one launch instead of two, a 3D
+                                 CGL step in two passes two instead of four)     */
     double alg_bytes_per_step;/* HBM bytes one step must move (all realizations)   */
     double site_updates_per_step; /* prod n[i] * realizations                      */
     double pass_bytes[4];     /* HBM bytes each kernel launch of a step must move,

@@ -254,23 +254,23 @@ setd_status Plan::init(const setd_desc& desc)
     return SETD_OK;
 }
 
-int Plan::passes_per_step() const
+int Plan::passes_per_step(bool general) const
 {
-    if (d.nl == NL_NONE || d.ndim == 1 || small) return 1;
-    return d.ndim == 2 || part3 ? 2 : 4;
+    if (d.nl == NL_NONE || d.ndim == 1 || (small && !general)) return 1;
+    return d.ndim == 2 || (part3 && !general) ? 2 : 4;
 }
 
 // HBM bytes each pass must move with the stored (2/3-pruned) arrays: one read
 // and one write of every array a pass cannot keep in LDS, at the unpadded
 // stored sizes.
-void Plan::pass_bytes(double* out) const
+void Plan::pass_bytes(double* out, bool general) const
 {
     for (int i = 0; i < 4; i++) out[i] = 0.0;
     const double e = (double)elt * R;
     const double kl = (double)g.kept[g.ndim - 1];
     const double st = (double)kept_modes;                 // stored modes
     const double hist = (d.order == 2 && !lean) ? 2.0 : 0.0;   // read + write F_{n-1} (lean: one carry array)
-    if (d.ndim == 1 || small) {
+    if (d.ndim == 1 || (small && !general)) {
         // a line or small lattice: state (and F_{n-1}) in and out once per launch, given per step
         // of a one-step launch
         out[0] = (2.0 + hist) * st * e;
@@ -298,7 +298,7 @@ void Plan::pass_bytes(double* out) const
     }
     const double small = (double)g.n[0] * g.kept[1] * kl;
     const double bigv = (double)g.n[0] * g.n[1] * kl;
-    if (part3) {
+    if (part3 && !general) {
         out[0] = 2.0 * bigv * e;                                // rows with the inner factor of axis 1
         out[1] = (2.0 * bigv + (2.0 + hist) * st) * e;          // axis 0 with the outer factor
         return;
@@ -317,10 +317,10 @@ void Plan::pass_bytes(double* out) const
     out[3] = (2.0 * small + (2.0 + hist) * st) * e;             // axis 0
 }
 
-double Plan::alg_bytes_per_step() const
+double Plan::alg_bytes_per_step(bool general) const
 {
     double b[4];
-    pass_bytes(b);
+    pass_bytes(b, general);
     double noise = 0.0;
     if (rsn_grid()) {
         // the noise transform: the last-axis pass writes its intermediate
@@ -1458,11 +1458,11 @@ setd_status setd_plan_info(const setd_plan* plan, setd_plan_info_t* info)
     info->spectral_len = p.nspec;
     info->kept_modes = p.kept_modes;
     info->nbins = p.nbins;
-    // an unbound plan gives the passes of the general path
-    info->passes_per_step = p.bound ? p.passes_per_step() : (p.small ? 2 : (p.part3 ? 4 : p.passes_per_step()));
-    info->alg_bytes_per_step = p.alg_bytes_per_step();
+    // an unbound plan gives the passes and bytes of the general path
+    info->passes_per_step = p.passes_per_step(!p.bound);
+    info->alg_bytes_per_step = p.alg_bytes_per_step(!p.bound);
     info->site_updates_per_step = (double)p.nreal * p.R;
-    p.pass_bytes(info->pass_bytes);
+    p.pass_bytes(info->pass_bytes, !p.bound);
     info->variants[0] = p.tune.row;
     info->variants[1] = p.tune.ax0;
     info->variants[2] = p.tune.ax1;

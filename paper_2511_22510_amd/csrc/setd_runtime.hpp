@@ -118,7 +118,7 @@ struct Plan {
     // queue pass i (launch order) of one step
     setd_status launch_pass(int i, const Item* items_dev, int nitems, int sub, hipStream_t s) const;
     setd_status profile_read(double* out, size_t cap, size_t* len);
-    void pass_bytes(double* out4) const;
+    void pass_bytes(double* out4, bool general = false) const;
     setd_status step(int64_t n);
     // n steps of every realization without per-pass events, split over two
     // streams when `split` is 2
@@ -145,8 +145,8 @@ struct Plan {
     // lean plans: carry Y = E phi + G eta_n of nitems items from items_dev,
     // n each realization's step index
     setd_status carry_init(const Item* items_dev, int nitems);
-    double alg_bytes_per_step() const;
-    int passes_per_step() const;
+    double alg_bytes_per_step(bool general = false) const;
+    int passes_per_step(bool general = false) const;   // general: as if neither small nor part3
 };
 
 // descriptor validation shared by plans and the server

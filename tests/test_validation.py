@@ -81,3 +81,17 @@ def test_plan_sizes(p, kept, nb, passes):
     assert info.kept_modes == kept and info.nbins == nb and info.passes_per_step == passes
     assert info.workspace_bytes > 0
     assert info.site_updates_per_step == float(p["realizations"]) * float(__import__("numpy").prod(p["n"]))
+
+
+@pytest.mark.parametrize("p,passes", [
+    (W.model_b([64, 64]), 2), (W.model_a([32, 64], precision=64), 2), (W.kpz([64, 32], history_readback=1), 2),
+    (W.cgl([256, 256, 256]), 4), (W.cgl([32, 64, 128]), 4), (W.cgl([32, 32, 32], precision=64), 4),
+    (W.model_b([128, 64]), 2), (W.model_a([256]), 1), (W.model_a([64, 64], nl="none"), 1)])
+def test_unbound_plan_record_describes_one_path(p, passes):
+    """Passes and bytes of an unbound plan are those of one path: as many byte
+    entries as passes, and their sum is the step's."""
+    from paper_2511_22510_amd import setd
+    st, info = _status(p)
+    assert st == setd.SETD_OK and info.passes_per_step == passes
+    b = list(info.pass_bytes)
+    assert sum(x > 0 for x in b) == passes and info.alg_bytes_per_step == sum(b)
