@@ -766,17 +766,16 @@ setd_status Plan::autotune()
 setd_status Plan::run_steps_on(int64_t n, int split, hipStream_t s)
 {
     const Item* items_dev = reinterpret_cast<const Item*>(ws + lay.items);
-    if (multi_step()) {
-        // the state stays in registers (and LDS): up to 256 steps per launch
-        for (int64_t left = n; left > 0; left -= 256) {
-            setd_status st = launch_steps(items_dev, R, 0, (int)std::min<int64_t>(left, 256), Record{0, 0}, s);
-            if (st != SETD_OK) return st;
-        }
-        return SETD_OK;
-    }
-    if (split != 2 || !aux || R < 2 || n <= 0) {
-        for (int64_t i = 0; i < n; i++) {
-            setd_status st = launch_step(items_dev, R, 0, s);
+    // the launches of one round of nitems items on a stream: a step, or up to
+    // 256 where the state stays in registers (and LDS)
+    const int64_t per = multi_step() ? 256 : 1;
+    auto round = [&](const Item* it, int nitems, int64_t left, hipStream_t on) {
+        return multi_step() ? launch_steps(it, nitems, 0, (int)std::min(left, per), Record{0, 0}, on)
+                            : launch_step(it, nitems, 0, on);
+    };
+    if (split != 2 || !can_split() || n <= 0) {
+        for (int64_t left = n; left > 0; left -= per) {
+            setd_status st = round(items_dev, R, left, s);
             if (st != SETD_OK) return st;
         }
         return SETD_OK;
@@ -785,9 +784,9 @@ setd_status Plan::run_steps_on(int64_t n, int split, hipStream_t s)
     SETD_HIP(hipEventRecord(ev_fork, s));
     SETD_HIP(hipStreamWaitEvent(aux, ev_fork, 0));
     setd_status st = SETD_OK;
-    for (int64_t i = 0; i < n && st == SETD_OK; i++) {
-        st = launch_step(items_dev, h, 0, s);
-        if (st == SETD_OK) st = launch_step(items_dev + h, R - h, 0, aux);
+    for (int64_t left = n; left > 0 && st == SETD_OK; left -= per) {
+        st = round(items_dev, h, left, s);
+        if (st == SETD_OK) st = round(items_dev + h, R - h, left, aux);
     }
     // join even after a failed launch, so that nothing is left running on aux
     SETD_HIP(hipEventRecord(ev_join, aux));
@@ -1466,7 +1465,7 @@ setd_status setd_plan_info(const setd_plan* plan, setd_plan_info_t* info)
     info->variants[0] = p.tune.row;
     info->variants[1] = p.tune.ax0;
     info->variants[2] = p.tune.ax1;
-    info->streams = (p.tune.split == 2 && p.aux) ? 2 : 1;
+    info->streams = (p.tune.split == 2 && p.can_split()) ? 2 : 1;
     info->graph_steps = p.graph_chunk;
     setd::axis_shape(p.d.precision, p.g.n[0], p.tune.ax0, &info->axis_tile[0], &info->axis_tile[1]);
     return SETD_OK;

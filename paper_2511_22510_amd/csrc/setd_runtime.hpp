@@ -109,6 +109,9 @@ struct Plan {
     // its own), recording the time-series window rec
     setd_status launch_steps(const Item* items_dev, int nitems, int sub, int n, const Record& rec, hipStream_t s) const;
     bool multi_step() const { return d.ndim == 1 || small; }
+    // whether calls of several steps can run in halves on two streams (real 1D
+    // lines pair their realizations, and a launch of lines is one in any case)
+    bool can_split() const { return aux && R >= 2 && d.ndim > 1; }
     // 2D/3D plans with real-space noise: its transform for the current step
     setd_status launch_noise(const Item* items_dev, int nitems, int sub, hipStream_t s) const;
     bool rsn_grid() const { return d.noise_space == 1 && d.ndim >= 2; }

@@ -279,3 +279,24 @@ def test_one_column_axis_0_tiles(kind, variant, monkeypatch):
         g, o = S.Plan(p), O.Sim(p)
         assert _trajectory_error(g, o, 2, (1, 1, 4, 6)) <= 1e-10
         g.close()
+
+
+@pytest.mark.parametrize("p,streams", [(W.model_b([64, 64], realizations=5), 2), (W.kpz([32, 64], realizations=2, ic_kind=1, ic_sigma=0.2), 2),
+                                       (W.model_b([128, 32], realizations=5), 2), (W.model_a([64, 64], realizations=1), 1),
+                                       (W.kpz([256], realizations=6, ic_kind=1, ic_sigma=0.2), 1), (W.cgl([64], realizations=3), 1)])
+def test_reported_streams_are_those_of_the_steps(p, streams, monkeypatch):
+    """With the split pinned, the record says two streams where the steps run
+    in halves on two and one where they cannot; the bits do not depend on it,
+    launches of 256 steps and a remainder included."""
+    S = _setd()
+    monkeypatch.setenv("SETD_VARIANT", "1,4,1")
+    one = S.Plan(p)
+    monkeypatch.setenv("SETD_SPLIT", "2")
+    two = S.Plan(p)
+    assert int(one.info.streams) == 1 and int(two.info.streams) == streams
+    for n in (5, 3, 300):
+        one.step(n)
+        two.step(n)
+        assert np.array_equal(one.get_all(), two.get_all())
+    one.close()
+    two.close()
