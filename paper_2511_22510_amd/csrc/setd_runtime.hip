@@ -270,10 +270,16 @@ void Plan::pass_bytes(double* out, bool general) const
     const double kl = (double)g.kept[g.ndim - 1];
     const double st = (double)kept_modes;                 // stored modes
     const double hist = (d.order == 2 && !lean) ? 2.0 : 0.0;   // read + write F_{n-1} (lean: one carry array)
-    if (d.ndim == 1 || (small && !general)) {
-        // a line or small lattice: state (and F_{n-1}) in and out once per launch, given per step
+    if (d.ndim == 1) {
+        // a line: state (and F_{n-1}) in and out once per launch, given per step
         // of a one-step launch
         out[0] = (2.0 + hist) * st * e;
+        return;
+    }
+    if (small && !general) {
+        // a small lattice: the same, and its intermediate (KPZ: both)
+        const double pre = (double)g.n[0] * kl * ((d.nl == NL_KPZ) ? 2.0 : 1.0);
+        out[0] = (2.0 * pre + (2.0 + hist) * st) * e;
         return;
     }
     if (d.nl == NL_NONE) {

@@ -300,3 +300,20 @@ def test_reported_streams_are_those_of_the_steps(p, streams, monkeypatch):
         assert np.array_equal(one.get_all(), two.get_all())
     one.close()
     two.close()
+
+
+@pytest.mark.parametrize("p,arrays", [(W.model_b([64, 32], realizations=3), 1), (W.kpz([64, 64], ic_kind=1), 2),
+                                      (W.model_a([32, 64], order=2, precision=64, history_readback=1), 1)])
+def test_bytes_of_a_small_lattice_launch(p, arrays):
+    """A one-step launch of a small lattice reads and writes its axis-0
+    intermediate (n_0 rows of the stored columns; KPZ two of them) and its
+    state, with the separate SETD2 storage F_{n-1} too."""
+    g = _setd().Plan(p)
+    info = g.info
+    n0, n1 = p["n"]
+    kc = (n1 - 1) // 3 + 1
+    modes = (2 * ((n0 - 1) // 3) + 1) * kc
+    val = p["precision"] // 4 * p["realizations"]
+    want = 2 * val * (arrays * n0 * kc + (2 if p.get("history_readback") else 1) * modes)
+    assert list(info.pass_bytes) == [want, 0, 0, 0] and info.alg_bytes_per_step == want
+    g.close()
