@@ -225,12 +225,17 @@ def setd_observe(plan, kind, cap, lib=None, allow_nonfinite=False):
 
 
 def setd_get_field(plan, r, nspec, lib=None, out=None):
-    """The spectrum of realization r (into out, 2 nspec doubles, if given)."""
-    lib = lib or load()
+    """The spectrum of realization r (into the first 2 nspec doubles of out, a
+    writeable C-contiguous float64 array, if given)."""
     if out is None:
         out = np.empty(2 * nspec, dtype=np.float64)
+    elif not isinstance(out, np.ndarray) or out.dtype != np.float64:
+        raise TypeError("out must be a float64 array")
+    elif not (out.flags.c_contiguous and out.flags.writeable and out.flags.aligned) or out.size < 2 * nspec:
+        raise ValueError("out must be C-contiguous, writeable and hold %d doubles" % (2 * nspec))
+    lib = lib or load()
     _check(lib, lib.setd_get_field(plan, int(r), out.ctypes.data_as(_D), out.size))
-    return out.view(np.complex128)
+    return out.reshape(-1)[: 2 * nspec].view(np.complex128)
 
 
 def setd_set_field(plan, r, arr, lib=None):

@@ -95,3 +95,34 @@ def test_unbound_plan_record_describes_one_path(p, passes):
     assert st == setd.SETD_OK and info.passes_per_step == passes
     b = list(info.pass_bytes)
     assert sum(x > 0 for x in b) == passes and info.alg_bytes_per_step == sum(b)
+
+
+def test_read_out_arrays_that_do_not_fit_are_refused():
+    """An array given for a field has to be what the C side writes: 2 nspec
+    doubles, contiguous and writeable.  Others are refused before the call."""
+    import numpy as np
+    from paper_2511_22510_amd import setd
+
+    class Lib:
+        calls = 0
+
+        def setd_get_field(self, plan, r, ptr, cap):
+            self.calls += 1
+            for i in range(16):
+                ptr[i] = float(i)
+            return setd.SETD_OK
+
+    lib, n = Lib(), 8
+    ro = np.zeros(16)
+    ro.flags.writeable = False
+    odd = np.frombuffer(bytearray(16 * 8 + 1), dtype=np.uint8)[1:].view(np.float64)
+    for bad in (np.zeros(16, np.float32), np.zeros(16, ">f8"), np.zeros(8, np.complex128), np.zeros(32)[::2],
+                np.zeros((4, 4)).T, np.zeros(15), ro, odd, [0.0] * 16):
+        with pytest.raises((TypeError, ValueError)):
+            setd.setd_get_field(None, 0, n, lib, bad)
+    assert lib.calls == 0
+    want = np.arange(16.0).view(np.complex128)
+    assert np.array_equal(setd.setd_get_field(None, 0, n, lib), want)
+    for good in (np.zeros(16), np.zeros(17), np.zeros((2, 8)), np.zeros((3, 16))[1]):
+        got = setd.setd_get_field(None, 0, n, lib, good)
+        assert np.array_equal(got, want) and np.shares_memory(got, good)
