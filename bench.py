@@ -218,7 +218,8 @@ def pass_roofline(r, p, names, traffic_workload=None):
     The per-pass segment always runs on one stream; when the plan steps the
     halves of its realizations on two streams, the uninstrumented step
     overlaps them, so no gap is subtracted (the bracketed durations are an
-    upper bound).  achieved = the pass model's bytes (survey_pass_bytes) /
+    upper bound).  achieved = the pass model's bytes (survey_pass_bytes; those
+    the passes move where a step takes fewer of them than the model) /
     duration; the bytes this build's storage moves (the plan's own pass bytes:
     a dealiased SETD2 plan keeps one carry array instead of phi and F_{n-1})
     are given beside."""
@@ -232,10 +233,11 @@ def pass_roofline(r, p, names, traffic_workload=None):
     gap = 0.0 if two_streams else max(0.0, (float(ev_avg.sum()) - steps_ev) / npass)
     avg = ev_avg - gap
     model = survey_pass_bytes(p)
-    if npass == 2 and len(model) == 4:
-        # the 3D step in two passes: the axis-1 passes of the model ride with the rows
-        model = [model[0] + model[1] + model[2], model[3]]
     moved = [float(info.pass_bytes[i]) for i in range(npass)]
+    if npass != len(model):
+        # a step in fewer passes than the model's (3D in two): no pass of the
+        # model is one of its launches, and each is rated on what it moves
+        model = moved
     dom = int(np.argmax(avg))
     passes = [{"kernel": names[i], "avg_us": float(avg[i] * 1e6), "avg_us_events": float(ev_avg[i] * 1e6),
                "alg_bytes": model[i], "moved_bytes": moved[i], "gbs": model[i] / avg[i] / 1e9,

@@ -140,3 +140,22 @@ def test_event_gap_is_subtracted_only_for_one_stream():
     assert abs(one["event_gap_us"] - 2.5) < 1e-9 and abs(one["avg_launch_us"] - 37.5) < 1e-9
     assert two["event_gap_us"] == 0.0 and abs(two["avg_launch_us"] - 40.0) < 1e-9
     assert one["step_streams"] == 1 and two["step_streams"] == 2
+
+
+def test_passes_that_the_model_does_not_know_are_rated_on_what_they_move():
+    """A 3D step in two passes is not credited with the bytes of the model's
+    axis-1 passes, which it does not make: both passes and the step are rated on
+    the plan's own bytes."""
+    import numpy as np
+    from paper_2511_22510_amd import workloads as W
+
+    class Info:
+        streams, pass_bytes = 2, [7e8, 1.05e9, 0.0, 0.0]
+
+    prof = np.array([[16.0, 100.0], [28.0, 100.0]])   # 160 and 280 us per launch
+    r = dict(info=Info(), ev=100 * 430e-6, steps=100, prof=prof)
+    rl, dom, _ = bench.pass_roofline(r, W.problem(W.CONFIG_CGL), ["rows", "axis0"])
+    assert dom == 1 and rl["alg_bytes_per_launch"] == rl["moved_bytes_per_launch"] == 1.05e9
+    for q, gbs in zip(rl["passes"], (7e8 / 160e-6 / 1e9, 1.05e9 / 280e-6 / 1e9)):
+        assert abs(q["gbs"] / gbs - 1) < 1e-12 and q["gbs"] == q["gbs_moved"]
+    assert rl["step_frac"] == rl["step_frac_moved"] and abs(rl["step_moved_bytes"] - 1.75e9) < 1
