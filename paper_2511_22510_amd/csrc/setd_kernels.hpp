@@ -2372,10 +2372,17 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
             }
             if (acta) pa[q] = na;
             if (actb) pb[q] = nb;
-            if (a.rec.slot) {
-                const int64_t o = a.rec.first + s * a.rec.slot;
-                if (acta) reinterpret_cast<cx<T>*>((char*)ia.phi + o)[m] = T(N) * na;
-                if (actb) reinterpret_cast<cx<T>*>((char*)ib.phi + o)[m] = T(N) * nb;
+        }
+        // (one branch a step: a branch per mode cost 4-10% of every step)
+        if (a.rec.slot) {
+            const int64_t o = a.rec.first + s * a.rec.slot;
+            cx<T>* const sa = reinterpret_cast<cx<T>*>((char*)ia.phi + o);
+            cx<T>* const sb = reinterpret_cast<cx<T>*>((char*)ib.phi + o);
+#pragma unroll
+            for (int q = 0; q < QS; q++) {
+                if (!stored(q)) continue;
+                if (acta) sa[mode_of(q)] = T(N) * pa[q];
+                if (actb) sb[mode_of(q)] = T(N) * pb[q];
             }
         }
         if constexpr (NW) __syncthreads();   // the draws of step s are read, those of s + 1 written
@@ -2426,7 +2433,10 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
 // Complex field, one realization per line: thread t keeps bins j = t + q N/8
 // of phi (FFT order).  KIND 0: CGL, F = -(1 + i beta) FFT[|phi|^2 phi];
 // 1: no nonlinearity.  The noise block t + qM (q < 4) serves bins q and 7 - q.
-template <typename T, int N, int PAD, int DM, int KIND, bool RS>
+// REC: a time-series window is open.  (Its stores, even behind a branch that is
+// never taken, cost the FP64 steps 5%: 5.8 against 5.5 us at 256 x 2048, 47.0
+// against 46.0 at x 16384.)
+template <typename T, int N, int PAD, int DM, int KIND, bool RS, bool REC>
 __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -2595,8 +2605,12 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
                 fp[q] = F[q];
             }
             if (act) p[q] = nw;
-            if (act && a.rec.slot)
-                reinterpret_cast<cx<T>*>((char*)it.phi + a.rec.first + s * a.rec.slot)[si[q]] = T(N) * nw;
+        }
+        if constexpr (REC) {
+            cx<T>* const smp = reinterpret_cast<cx<T>*>((char*)it.phi + a.rec.first + s * a.rec.slot);
+#pragma unroll
+            for (int q = 0; q < 8; q++)
+                if (act && si[q] >= 0) smp[si[q]] = T(N) * p[q];
         }
     }
     cx<T>* pv = reinterpret_cast<cx<T>*>(it.prev);

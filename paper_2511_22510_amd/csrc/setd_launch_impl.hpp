@@ -464,8 +464,14 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
         a.nlines = nitems;
         const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
         const size_t lds = (size_t)LPB * ((RS || DM == 2) ? 2 : 1) * LL * sizeof(cx<T>);
-        if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS>), grid, dim3(BT), lds, s, a);
-        else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS>), grid, dim3(BT), lds, s, a);
+        const bool record = mode == MODE_STEP && rec.slot != 0;
+        if (nl == NL_NONE) {
+            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, true>), grid, dim3(BT), lds, s, a);
+            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, false>), grid, dim3(BT), lds, s, a);
+        } else {
+            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, true>), grid, dim3(BT), lds, s, a);
+            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, false>), grid, dim3(BT), lds, s, a);
+        }
         return hipGetLastError();
     }
     a.nlines = (nitems + 1) / 2;

@@ -317,3 +317,33 @@ def test_bytes_of_a_small_lattice_launch(p, arrays):
     want = 2 * val * (arrays * n0 * kc + (2 if p.get("history_readback") else 1) * modes)
     assert list(info.pass_bytes) == [want, 0, 0, 0] and info.alg_bytes_per_step == want
     g.close()
+
+
+@pytest.mark.parametrize("n,prec,dealias,kw", [(8, 64, 1, {}), (64, 32, 0, {}), (256, 64, 1, {}), (256, 32, 2, {}), (512, 64, 2, {}),
+                                               (1024, 32, 1, {}), (1024, 64, 0, {}), (128, 64, 1, dict(nl="none")), (64, 32, 0, dict(nl="none", order=1))])
+def test_open_window_leaves_complex_lines_alike(n, prec, dealias, kw):
+    """Complex lines record an open window in an instantiation of their own: a
+    trajectory has the same bits with and without the window, before, during and
+    after it, and the window's correlations are the oracle's."""
+    S = _setd()
+    p = W.cgl([n], precision=prec, dealias=dealias, realizations=5, seed=61, ic_sigma=0.3, **kw)
+    plain, rec = S.Plan(p), S.Plan(dict(p, series_len=8))
+    for g in (plain, rec):
+        g.step(3)
+    rec.observe(S.OBS_SERIES_START)
+    for k in (2, 1, 9, 4):
+        plain.step(k)
+        rec.step(k)
+        assert np.array_equal(plain.get_all(), rec.get_all())
+    o = O.Sim(p)
+    o.step(3)
+    o.series_start(8)
+    o.step(16)
+    C, xr, xi, cnt = rec.spectrum()
+    oC, oxr, oxi, ocnt = o.spectrum()
+    tol = 1e-10 if prec == 64 else 2e-4
+    assert np.array_equal(cnt, ocnt)
+    for a, b in ((C, oC), (xr, oxr), (xi, oxi)):
+        assert float(np.max(np.abs(a - b))) <= tol * float(np.max(np.abs(b)))
+    plain.close()
+    rec.close()
