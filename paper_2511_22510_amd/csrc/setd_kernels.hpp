@@ -1972,8 +1972,8 @@ __device__ __forceinline__ void line1d_tw(Line1dTw<T, N, KIND>& tw, int t, const
 // and Model B with its k^2 in the prefactor), 1: KPZ ((lambda/2) h'^2 from the
 // line of h + i h' per realization pair), 2: no nonlinearity.
 // Bound by VALU issue where the lines fill the chip.  us per step, before the
-// exchanges ordered by wavefront, the scaled state and the tables shared by the
-// pair / now: Model A N = 256 x 16384 8.9 / 6.2-6.7, KPZ N = 1024 x 4096 11.2 / 9.6.
+// exchanges ordered by wavefront and the tables shared by the pair / now: Model
+// A N = 256 x 16384 8.4 / 5.9, KPZ N = 1024 x 16384 43.8 / 30.8.
 // Threads of a block: a line of two wavefronts (N = 1024) has block barriers and
 // takes a block of its own, so that no other line waits at them.
 // A lone wavefront on its SIMD is bound by its own instructions, a third of them
@@ -2063,9 +2063,7 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
         return;
     }
 
-    // state, F_{n-1}, coefficients and steps of both realizations.  The launch
-    // holds the state, F_{n-1} and G times 1/N (a power of two, so exactly):
-    // the inverse transform then gives the field itself.
+    // state, F_{n-1}, coefficients and steps of both realizations
     cx<T> fa[QS], fb[QS];
     Coef<T> cf[QS];
     const cx<T>* phia0 = reinterpret_cast<const cx<T>*>(ia.phi);
@@ -2082,16 +2080,15 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
         if (!stored(q)) continue;
         const int m = mode_of(q);
         if (va) cf[q] = load_coef_t<T, false>(ia.coef, m);   // real fields: real tables, keyed by |a|
-        cf[q].G *= inv;
         // a realization that does not step in this launch is no partner: its
         // channel stays zero, as for the missing partner of an odd count
         if (acta) {
-            pa[q] = inv * phia0[m];
-            if (o2 && hpa) fa[q] = inv * preva[m];
+            pa[q] = phia0[m];
+            if (o2 && hpa) fa[q] = preva[m];
         }
         if (actb) {
-            pb[q] = inv * phib0[m];
-            if (o2 && hpb) fb[q] = inv * prevb[m];
+            pb[q] = phib0[m];
+            if (o2 && hpb) fb[q] = prevb[m];
         }
         if (m == 0 || 2 * m == N) {
             pa[q].y = T(0);
@@ -2202,16 +2199,17 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
 #pragma unroll 1
     for (int s = 0; s < (drawer ? 0 : a.nsteps); s++) {
         if constexpr (KIND != 2) {
-            // pack the two half spectra (KPZ: of h and h' per realization)
+            // pack the two half spectra (KPZ: of h and h' per realization), times
+            // 1/N: the inverse transform then gives the field itself
             exchange_sync<WV>();
 #pragma unroll
             for (int q = 0; q < QS; q++) {
                 if (q == 4 && t != 0) continue;
                 const int m = mode_of(q);
-                cx<T> A = pa[q], B = pb[q];
+                cx<T> A = inv * pa[q], B = inv * pb[q];
                 if constexpr (KIND == 1) {
                     // h' = i k h, the Nyquist derivative dropped
-                    const T kk = (2 * m == N) ? T(0) : (T)m;
+                    const T kk = (2 * m == N) ? T(0) : inv * (T)m;
                     A = {-kk * dk * pa[q].y, kk * dk * pa[q].x};
                     B = {-kk * dk * pb[q].y, kk * dk * pb[q].x};
                 }
@@ -2326,7 +2324,7 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
                 const cx<T> wb = {Zk.y + Zm.y, Zm.x - Zk.x};
                 // Model B: -u k^2; the others a constant
                 const T kq = dk * (T)k;
-                const T sc = T(0.5) * inv * ((ia.nl == NL_PHI3_CONS) ? -(T)ia.par0 * (kq * kq) : pr);
+                const T sc = T(0.5) * ((ia.nl == NL_PHI3_CONS) ? -(T)ia.par0 * (kq * kq) : pr);
                 F1[q] = sc * wa;
                 F2[q] = sc * wb;
             }
@@ -2381,8 +2379,8 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
 #pragma unroll
             for (int q = 0; q < QS; q++) {
                 if (!stored(q)) continue;
-                if (acta) sa[mode_of(q)] = T(N) * pa[q];
-                if (actb) sb[mode_of(q)] = T(N) * pb[q];
+                if (acta) sa[mode_of(q)] = pa[q];
+                if (actb) sb[mode_of(q)] = pb[q];
             }
         }
         if constexpr (NW) __syncthreads();   // the draws of step s are read, those of s + 1 written
@@ -2401,16 +2399,14 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
         if (!stored(q)) continue;
         const int m = mode_of(q);
         if (acta) {
-            const cx<T> h = T(N) * pa[q];
-            phia[m] = h;
-            if (o2 && a.nsteps > 0) pva[m] = T(N) * fa[q];
-            bada |= !(isfinite(h.x) && isfinite(h.y));
+            phia[m] = pa[q];
+            if (o2 && a.nsteps > 0) pva[m] = fa[q];
+            bada |= !(isfinite(pa[q].x) && isfinite(pa[q].y));
         }
         if (actb) {
-            const cx<T> h = T(N) * pb[q];
-            phib[m] = h;
-            if (o2 && a.nsteps > 0) pvb[m] = T(N) * fb[q];
-            badb |= !(isfinite(h.x) && isfinite(h.y));
+            phib[m] = pb[q];
+            if (o2 && a.nsteps > 0) pvb[m] = fb[q];
+            badb |= !(isfinite(pb[q].x) && isfinite(pb[q].y));
         }
     }
     if (bada) atomicOr(&ia.ctrl->nonfinite, 1);
@@ -2459,7 +2455,10 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
     const bool act = valid && a.sub < it.steps;
     Line1dTw<T, N, 2> tw;
     line1d_tw<T, N, 2>(tw, t, twid<T>(it.tw0));
-    const T inv = (T)it.inv_vol;
+    // N^-3 (a power of two): |phi|^2 phi from the unscaled inverse transform
+    // N phi, whose square overflows only where the cube does
+    const T inv3 = (T)it.inv_vol * (T)it.inv_vol * (T)it.inv_vol;
+    (void)inv3;
     const int kept = g.kept[0], kp = g.kp[0];
     int si[8];
 #pragma unroll
@@ -2493,13 +2492,11 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
         p[q] = fp[q] = czero<T>();
         cf[q] = Coef<T>{czero<T>(), czero<T>(), czero<T>(), T(0)};
         if (si[q] < 0 || !valid) continue;
-        // state, F_{n-1} and G times 1/N, as in k_line1d_real
-        p[q] = inv * phi[si[q]];
-        if (o2 && hp) fp[q] = inv * prev0[si[q]];
+        p[q] = phi[si[q]];
+        if (o2 && hp) fp[q] = prev0[si[q]];
         cf[q] = load_coef_t<T, true>(it.coef, coef_key(it, sgn_idx(t + q * M, N), 0, 0));   // complex tables
-        cf[q].G *= inv;
     }
-    const cx<T> pref = inv * nl_pref<T>(it, T(0));
+    const cx<T> pref = nl_pref<T>(it, T(0));
     const T rsq = (T)(1.0 / sqrt((double)N));
     bool bad = false;
 #pragma unroll 1
@@ -2537,7 +2534,7 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
 #pragma unroll
                     for (int q = 0; q < 8; q++) {
                         const T x = z[u][q].x, y = z[u][q].y;
-                        const T m2 = x * x + y * y;
+                        const T m2 = inv3 * (x * x + y * y);
                         z[u][q] = {m2 * x, m2 * y};
                     }
                 }
@@ -2549,7 +2546,7 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     const T x = z[0][q].x, y = z[0][q].y;
-                    const T m2 = x * x + y * y;
+                    const T m2 = inv3 * (x * x + y * y);
                     z[0][q] = {m2 * x, m2 * y};
                 }
             }
@@ -2610,7 +2607,7 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
             cx<T>* const smp = reinterpret_cast<cx<T>*>((char*)it.phi + a.rec.first + s * a.rec.slot);
 #pragma unroll
             for (int q = 0; q < 8; q++)
-                if (act && si[q] >= 0) smp[si[q]] = T(N) * p[q];
+                if (act && si[q] >= 0) smp[si[q]] = p[q];
         }
     }
     cx<T>* pv = reinterpret_cast<cx<T>*>(it.prev);
@@ -2618,10 +2615,9 @@ __global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
 #pragma unroll
         for (int q = 0; q < 8; q++) {
             if (si[q] < 0) continue;
-            const cx<T> h = T(N) * p[q];
-            phi[si[q]] = h;
-            if (o2 && a.nsteps > 0) pv[si[q]] = T(N) * fp[q];
-            bad |= !(isfinite(h.x) && isfinite(h.y));
+            phi[si[q]] = p[q];
+            if (o2 && a.nsteps > 0) pv[si[q]] = fp[q];
+            bad |= !(isfinite(p[q].x) && isfinite(p[q].y));
         }
     }
     if (bad) atomicOr(&it.ctrl->nonfinite, 1);

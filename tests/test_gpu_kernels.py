@@ -347,3 +347,34 @@ def test_open_window_leaves_complex_lines_alike(n, prec, dealias, kw):
         assert float(np.max(np.abs(a - b))) <= tol * float(np.max(np.abs(b)))
     plain.close()
     rec.close()
+
+
+@pytest.mark.parametrize("n,p", [(256, W.model_a([256], h=1e-3)), (1024, W.kpz([1024], h=1e-3)), (1024, W.cgl([1024], dealias=0)),
+                                 (64, W.model_b([64], h=1e-4, dealias=2)), (1024, W.model_a([1024], nl="none", h=1e-3, order=2)),
+                                 (512, W.cgl([512], nl="none"))])
+def test_lines_keep_small_single_precision_states(n, p):
+    """A line's state is held as it is stored: modes near the smallest normal
+    single-precision numbers (1.2e-38) evolve with a float's relative precision
+    (at most four roundings of 2^-24 a step), no bits lost to a scaled copy."""
+    S = _setd()
+    p = dict(p, precision=32, realizations=2, noise_D=0.0, ic_kind=0)
+    g, o = S.Plan(p), O.Sim(p)
+    rng = np.random.default_rng(5)
+    shape = W.spectral_shape(p)
+    for r in range(2):
+        x = 3e-37 * np.exp(2j * np.pi * rng.random(shape)) * (1.0 + rng.random(shape))
+        if not p["complex_field"]:
+            x[0] = x[0].real
+            x[-1] = x[-1].real
+        x = x.astype(np.complex64).astype(np.complex128)
+        g.set(r, x)
+        o.set(r, x)
+    steps = 12
+    g.step(steps)
+    o.step(steps)
+    for r in range(2):
+        a, b = g.get(r), o.get(r)
+        m = np.abs(b) > 1e-37
+        assert m.sum() > n // 8
+        assert float(np.max(np.abs(a - b)[m] / np.abs(b)[m])) <= (4 * steps + 2) * 2.0 ** -24
+    g.close()
