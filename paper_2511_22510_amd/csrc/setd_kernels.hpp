@@ -1974,20 +1974,24 @@ __device__ __forceinline__ void line1d_tw(Line1dTw<T, N, KIND>& tw, int t, const
 // Bound by VALU issue where the lines fill the chip.  us per step, before the
 // exchanges ordered by wavefront and the tables shared by the pair / now: Model
 // A N = 256 x 16384 8.4 / 5.9, KPZ N = 1024 x 16384 43.8 / 30.8.
-// Threads of a block: a line of two wavefronts (N = 1024) has block barriers and
-// takes a block of its own, so that no other line waits at them.
+// Threads of a block: a line of two wavefronts (N = 1024) whose step transforms
+// has block barriers and takes a block of its own, so that no other line waits
+// at them.  Steps without a transform (XF false: no nonlinearity, Fourier noise)
+// have none, and blocks of 256 spread evenly over the SIMDs: FP64, 1024 sites,
+// blocks of 128 / 256: real x 1024 4.9 / 2.8, x 8192 23.7 / 18.9, complex x 512
+// 4.9 / 3.0 us per step.
 // A lone wavefront on its SIMD is bound by its own instructions, a third of them
 // the noise: NW draws it in a second wavefront, one step ahead through LDS, with
 // one block barrier a step (the same values, so the same bits).
-constexpr int line1d_threads(int N) { return N / 8 > 64 ? N / 8 : 256; }
+constexpr int line1d_threads(int N, bool XF) { return XF && N / 8 > 64 ? N / 8 : 256; }
 
-template <typename T, int N, int PAD, int DM, int KIND, bool RS, bool NW>
-__global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Line1dArgs a)
+template <typename T, int N, int PAD, int DM, int KIND, bool RS, bool NW, int BT = NW ? 128 : line1d_threads(N, KIND != 2 || RS)>
+__global__ void __launch_bounds__(BT) k_line1d_real(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
-    constexpr int CT = NW ? 64 : line1d_threads(N);   // threads that step lines
+    constexpr int CT = NW ? 64 : BT;             // threads that step lines
     constexpr int LPB = CT / TPL;
     constexpr int LL = lds_len<N, PAD>();
     constexpr int QS = DA ? 3 : (PS ? 4 : 5);    // register slots of stored modes
@@ -2433,12 +2437,12 @@ __global__ void __launch_bounds__(NW ? 128 : line1d_threads(N)) k_line1d_real(Li
 // never taken, cost the FP64 steps 5%: 5.8 against 5.5 us at 256 x 2048, 47.0
 // against 46.0 at x 16384.)
 template <typename T, int N, int PAD, int DM, int KIND, bool RS, bool REC>
-__global__ void __launch_bounds__(line1d_threads(N)) k_line1d_cplx(Line1dArgs a)
+__global__ void __launch_bounds__(line1d_threads(N, KIND == 0 || RS)) k_line1d_cplx(Line1dArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr bool DA = DM == 1, PS = DM == 2;   // 2/3 truncation, phase shift
     constexpr int TPL = N / 8, M = N / 8;
-    constexpr int LPB = line1d_threads(N) / TPL;
+    constexpr int LPB = line1d_threads(N, KIND == 0 || RS) / TPL;
     constexpr bool WV = N <= 512;   // a line lies in one wavefront
     constexpr int LL = lds_len<N, PAD>();
     const Geo& g = a.g;

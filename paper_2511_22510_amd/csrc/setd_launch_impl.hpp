@@ -450,8 +450,11 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
 {
     // FP32 lines pad LDS by one slot per 8 (fewer bank conflicts in the
     // exchanges); FP64 lines would exceed 64 KiB of LDS with it
-    constexpr int TPL = N / 8, BT = line1d_threads(N), LPB = BT / TPL, PAD = sizeof(T) == 4 ? 3 : 0;
+    constexpr int TPL = N / 8, PAD = sizeof(T) == 4 ? 3 : 0;
     constexpr int LL = lds_len<N, PAD>();
+    // the kernel's block: a step transforms unless it is linear with Fourier noise
+    const int bt = nl == NL_NONE ? line1d_threads(N, RS) : line1d_threads(N, true);
+    const int lpb = bt / TPL;
     Line1dArgs a;
     a.g = g;
     a.items = items;
@@ -462,15 +465,15 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
     a.rec = rec;
     if (g.cplx) {
         a.nlines = nitems;
-        const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
-        const size_t lds = (size_t)LPB * ((RS || DM == 2) ? 2 : 1) * LL * sizeof(cx<T>);
+        const dim3 grid((unsigned)((a.nlines + lpb - 1) / lpb));
+        const size_t lds = (size_t)lpb * ((RS || DM == 2) ? 2 : 1) * LL * sizeof(cx<T>);
         const bool record = mode == MODE_STEP && rec.slot != 0;
         if (nl == NL_NONE) {
-            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, true>), grid, dim3(BT), lds, s, a);
-            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, false>), grid, dim3(BT), lds, s, a);
+            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, true>), grid, dim3(bt), lds, s, a);
+            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 1, RS, false>), grid, dim3(bt), lds, s, a);
         } else {
-            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, true>), grid, dim3(BT), lds, s, a);
-            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, false>), grid, dim3(BT), lds, s, a);
+            if (record) hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, true>), grid, dim3(bt), lds, s, a);
+            else hipLaunchKernelGGL((k_line1d_cplx<T, N, PAD, DM, 0, RS, false>), grid, dim3(bt), lds, s, a);
         }
         return hipGetLastError();
     }
@@ -491,11 +494,25 @@ static hipError_t launch_line1d_n(const Geo& g, const Item* items, int nitems, i
             return hipGetLastError();
         }
     }
-    const dim3 grid((unsigned)((a.nlines + LPB - 1) / LPB));
-    const size_t lds = (size_t)LPB * 2 * LL * sizeof(cx<T>);
-    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS, false>), grid, dim3(BT), lds, s, a);
-    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS, false>), grid, dim3(BT), lds, s, a);
-    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS, false>), grid, dim3(BT), lds, s, a);
+    // Linear FP64 lines of 1024 sites with site noise have registers to spare for
+    // two wavefronts per SIMD, and launches of more than half and at most one
+    // wavefront per SIMD then pair the two-wavefront blocks up on half the SIMDs:
+    // blocks of 256 take one wavefront on each.  us per step at 520 / 1024
+    // realizations: pairs 7.7 / 7.7, blocks of 256 5.6 / 5.7 (pairs at 512: 4.9).
+    if constexpr (RS && TPL > 64 && sizeof(T) == 8) {
+        const long w = (long)a.nlines * TPL / 64;
+        if (nl == NL_NONE && mode == MODE_STEP && w > 512 && w <= 1024) {
+            constexpr int LPB = 256 / TPL;
+            hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS, false, 256>), dim3((unsigned)((a.nlines + LPB - 1) / LPB)),
+                               dim3(256), (size_t)LPB * 2 * LL * sizeof(cx<T>), s, a);
+            return hipGetLastError();
+        }
+    }
+    const dim3 grid((unsigned)((a.nlines + lpb - 1) / lpb));
+    const size_t lds = (size_t)lpb * 2 * LL * sizeof(cx<T>);
+    if (nl == NL_KPZ) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 1, RS, false>), grid, dim3(bt), lds, s, a);
+    else if (nl == NL_NONE) hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 2, RS, false>), grid, dim3(bt), lds, s, a);
+    else hipLaunchKernelGGL((k_line1d_real<T, N, PAD, DM, 0, RS, false>), grid, dim3(bt), lds, s, a);
     return hipGetLastError();
 }
 

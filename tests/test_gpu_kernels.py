@@ -378,3 +378,31 @@ def test_lines_keep_small_single_precision_states(n, p):
         assert m.sum() > n // 8
         assert float(np.max(np.abs(a - b)[m] / np.abs(b)[m])) <= (4 * steps + 2) * 2.0 ** -24
     g.close()
+
+
+@pytest.mark.parametrize("kind,kw", [("model_a", dict(nl="none", noise_space=1)), ("model_a", dict(nl="none", noise_space=1, dealias=0)),
+                                     ("model_a", dict(nl="none")), ("cgl", dict(nl="none")), ("kpz", dict(noise_space=1))])
+@pytest.mark.parametrize("prec", [64, 32])
+def test_lines_of_two_wavefronts_in_any_block(kind, kw, prec):
+    """Lines of 1024 sites take blocks of one or two lines by what their steps
+    do and how many there are (one, a part and most of a wavefront per SIMD,
+    more): a realization's bits do not depend on it, and follow the oracle.
+    (Real lines pair realizations 2l and 2l + 1 in one transform, so the last of
+    an odd count has other roundings: the first pair is compared.)"""
+    S = _setd()
+    out = []
+    for R in (3, 511, 515, 1024, 1030):
+        p = dict(getattr(W, kind)([1024], precision=prec, realizations=R, order=2, seed=71, ic_kind=1, ic_sigma=0.2), **kw)
+        g = S.Plan(p)
+        g.step(2)
+        g.step(9)
+        out.append([g.get(r) for r in range(2)])
+        if R == 515:
+            for r in (0, 513, 514):
+                o = O.Sim(p, r_first=r, r_count=1)
+                o.step(11)
+                assert float(np.linalg.norm(g.get(r) - o.get(0))) <= (1e-10 if prec == 64 else 2e-4) * float(np.linalg.norm(o.get(0)))
+        g.close()
+    for b in out[1:]:
+        for x, y in zip(out[0], b):
+            assert np.array_equal(x, y)
