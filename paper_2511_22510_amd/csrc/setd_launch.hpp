@@ -96,6 +96,21 @@ inline bool small2d_ok(const Geo& g, int nl)
     if (g.ndim != 2 || g.cplx || g.dealias != 1 || g.rsn || nl == NL_NONE) return false;
     return (g.n[0] == 32 || g.n[0] == 64) && (g.n[1] == 32 || g.n[1] == 64);
 }
+// Realizations up to which a plan steps in that kernel.  With many more
+// workgroups than CUs it is bound by the exchanges of its short lines and loses to
+// the two passes, unless the lattice is 64 x 64.  Time of the two passes over its
+// own, at 2048 / 3072 / 5120 / 8192 realizations:
+//   64 x 64, FP32 and FP64           1.26-1.6 / 1.15-1.5  / 1.1-1.5   / 1.1-1.6
+//   32 x 32, FP32 (KPZ)              1.9 (1.7) / 1.6 (1.4) / 1.15 (1.0) / 0.94 (0.84)
+//   FP64 with a 32-point axis (KPZ)  1.2-1.5 (0.95-1.3) / 1.0-1.25 (0.9-1.2) / 0.9-1.07 (0.85-1.0) / 0.9-1.07 (0.8-1.0)
+//   32 x 64, 64 x 32, FP32 (KPZ)     1.15-1.4 (1.06-1.15) / 0.96-1.18 (0.85-1.04) / 0.76-1.1 (0.7-1.0) / 0.7-0.94 (0.6-0.8)
+inline int small2d_realizations(const Geo& g, int nl)
+{
+    if (g.n[0] == 64 && g.n[1] == 64) return 1 << 30;
+    if (g.prec == 64) return 3072;
+    if (g.n[0] == 32 && g.n[1] == 32) return 5120;
+    return nl == NL_KPZ ? 2048 : 3072;
+}
 template <typename T>
 hipError_t launch_small2d(const Geo& g, const Item* items, int nitems, int sub, int nsteps, int nl, bool lean,
                           const Record& rec, hipStream_t s);

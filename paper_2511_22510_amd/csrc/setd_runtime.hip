@@ -198,7 +198,7 @@ setd_status Plan::init(const setd_desc& desc)
     lean = d.ndim >= 2 && d.order == 2 && !d.history_readback && d.nl != NL_NONE && !d.noise_space &&
            axis0_register_ok(g, elt / 2);
     part3 = part3_ok(g, lean, d.nl);
-    small = small2d_ok(g, d.nl);
+    small = small2d_ok(g, d.nl) && R <= small2d_realizations(g, d.nl);
 
     // workspace layout, every buffer 256-byte aligned
     size_t off = 0;

@@ -86,7 +86,7 @@ struct Plan {
     // SETD2 storage: the carry Y_n = E phi_n + w_b F_{n-1} + G eta_n in the
     // F_{n-1} array, phi recovered from pre when read (phi_valid tracks it)
     bool lean = false;
-    bool small = false;           // 2D steps in one kernel (small2d_ok)
+    bool small = false;           // 2D steps in one kernel (small2d_ok, small2d_realizations)
     bool part3 = false;           // 3D step in two passes (part3_ok); the line buffer holds their array
     bool phi_valid = true;
     int64_t step_host = 0;        // steps queued so far (mirror of the device counter)

@@ -253,7 +253,8 @@ setd_status setd_server::tick(std::vector<Job*>& act, int* steps_taken)
     for (Job* j : act) {
         j->steps_tick = (int)std::min<int64_t>(chunk, j->nsteps - j->done_steps);
         maxk = std::max(maxk, j->steps_tick);
-        classes[class_key(*j->plan)].push_back(j);
+        // (a job steps by the path of its own plan, whatever runs beside it)
+        classes[class_key(*j->plan) + (j->plan->small ? "|small" : "")].push_back(j);
     }
     // item tables, one contiguous run per class.  A real 1D line pairs
     // realizations 2l and 2l + 1 in one transform, whose rounding couples

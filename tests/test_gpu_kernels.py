@@ -406,3 +406,41 @@ def test_lines_of_two_wavefronts_in_any_block(kind, kw, prec):
     for b in out[1:]:
         for x, y in zip(out[0], b):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n,prec,kind,limit", [((32, 32), 64, "model_b", 3072), ((32, 32), 32, "model_a", 5120), ((64, 32), 32, "kpz", 2048),
+                                               ((32, 64), 32, "model_b", 3072), ((64, 64), 32, "model_b", None)])
+def test_many_realizations_of_a_small_lattice_take_two_passes(n, prec, kind, limit):
+    """Up to a number of realizations a small lattice steps in one kernel, above
+    it (never at 64 x 64) in two passes: both follow the oracle, from the first
+    realization to the last."""
+    S = _setd()
+    for R in ((limit, limit + 1) if limit else (6000,)):
+        p = getattr(W, kind)(list(n), precision=prec, realizations=R, order=2, seed=81, ic_kind=1, ic_sigma=0.2)
+        g = S.Plan(p)
+        assert int(g.info.passes_per_step) == (2 if limit and R > limit else 1)
+        g.step(1)
+        g.step(6)
+        for r in (0, R // 2, R - 1):
+            o = O.Sim(p, r_first=r, r_count=1)
+            o.step(7)
+            assert float(np.linalg.norm(g.get(r) - o.get(0))) <= (1e-10 if prec == 64 else 2e-4) * float(np.linalg.norm(o.get(0)))
+        g.close()
+
+
+def test_small_lattice_jobs_keep_the_path_of_their_own_plan():
+    """Jobs of one lattice whose plans take different paths (few and many
+    realizations) run side by side in a server, each bitwise its solo run."""
+    S = _setd()
+    jobs = [(W.model_b([32, 32], realizations=3, seed=91), 60), (W.model_b([32, 32], realizations=5121, seed=92), 40),
+            (W.model_b([32, 32], realizations=2, seed=93), 25)]
+    srv = S.Server(512 << 20)
+    ids = [srv.submit(p, k) for p, k in jobs]
+    srv.drain()
+    for j, (p, k) in zip(ids, jobs):
+        solo = S.Plan(p)
+        solo.step(k)
+        for r in (0, p["realizations"] // 2, p["realizations"] - 1):
+            assert np.array_equal(srv.get(j, r), solo.get(r))
+        solo.close()
+    srv.close()
