@@ -324,10 +324,13 @@ setd_status setd_server::tick(std::vector<Job*>& act, int* steps_taken)
                 q_launches += 2;
                 q_shared += 2;
             } else if (launches[units[u]].rep->small) {
-                // one launch takes all of the tick's steps
-                if (sub > 0) continue;
+                // a launch takes up to 256 of the tick's steps (about 1 ms: a
+                // tick of small lattices alone has up to 1024), so that the
+                // units behind it on its lane do not wait for all of them
+                constexpr int PIECE = 256;
+                if (sub % PIECE != 0) continue;
                 const Launch& L = launches[units[u]];
-                lst = L.rep->launch_steps(items_dev + L.first, L.n, 0, maxk, Record{0, 0}, ls);
+                lst = L.rep->launch_steps(items_dev + L.first, L.n, sub, std::min(PIECE, maxk - sub), Record{0, 0}, ls);
                 q_launches += 1;
             } else {
                 const Launch& L = launches[units[u]];

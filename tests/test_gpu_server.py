@@ -234,3 +234,21 @@ def test_uneven_lattices_share_launches(multi, monkeypatch):
         say("job", jid, p["nl"], p["n"], "oracle err", err)
         assert err <= 2e-4
     srv.close()
+
+
+def test_small_lattice_launches_take_at_most_256_steps():
+    """A tick of a small-lattice class of hundreds of steps is queued in launches
+    of at most 256, so that a class behind it on its lane can start."""
+    S = _setd()
+    srv = S.Server(64 << 20)
+    p = W.model_b([64, 64], realizations=2, seed=3)
+    j = srv.submit(p, 2000)
+    srv.drain()
+    ticks, launches, _ = srv.stats()[:3]
+    solo = S.Plan(p)
+    solo.step(2000)
+    assert np.array_equal(srv.get(j, 1), solo.get(1))
+    assert 256 * launches >= 2000 and launches >= ticks
+    solo.close()
+    srv.close()
+
