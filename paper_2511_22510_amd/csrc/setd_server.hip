@@ -378,7 +378,11 @@ void setd_server::run()
             admit_locked(admitted);
             for (setd_job id : active) act.push_back(jobs[id].get());
         }
-        // bind the new jobs: tables, tuned variants, initial condition
+        // bind the new jobs: tables, tuned variants, initial condition.  The
+        // time of a step was that of the jobs before them: measured anew (a
+        // short class alone would give the first ticks with a long one beside
+        // it many times the target)
+        if (!admitted.empty()) est_step_s = 0.0;
         for (Job* j : admitted) {
             setd_status st = j->plan->bind(arena + j->off, j->bytes, stream);
             if (st != SETD_OK) {

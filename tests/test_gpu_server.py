@@ -252,3 +252,22 @@ def test_small_lattice_launches_take_at_most_256_steps():
     solo.close()
     srv.close()
 
+
+def test_step_time_is_measured_anew_when_jobs_join(monkeypatch):
+    """The steps of a tick come from the measured time of a step of the jobs
+    that ran; a tick that jobs join is short again, as the very first one, since
+    that time was not theirs."""
+    import time
+    S = _setd()
+    monkeypatch.setenv("SETD_SERVER_TICK", "1000")   # the most steps a tick takes from the second on
+    srv = S.Server(256 << 20)
+    first, most, n = 16, 1024, 200
+    srv.submit(W.model_b([64, 64], realizations=1, seed=3), first + most * n)
+    t0 = time.time()
+    while srv.stats()[0] < 2 and time.time() - t0 < 20:
+        time.sleep(1e-4)
+    assert 2 <= srv.stats()[0] <= n
+    j = srv.submit(W.model_a([128, 128], precision=32, order=2, seed=4), 100)
+    srv.drain()
+    assert int(srv.stats()[0]) == n + 2 and int(S.setd_job_times(srv.h, j, srv.lib)[3]) == 100
+    srv.close()
