@@ -36,6 +36,12 @@ template <typename T>
 __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.x - b.x, a.y - b.y}; }
 template <typename T>
 __device__ __forceinline__ cx<T> operator*(T s, cx<T> a) { return {s * a.x, s * a.y}; }
+// s a + b, contracted
+template <typename T>
+__device__ __forceinline__ cx<T> fma_cx(T s, cx<T> a, cx<T> b)
+{
+    return {__builtin_elementwise_fma(s, a.x, b.x), __builtin_elementwise_fma(s, a.y, b.y)};
+}
 template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 // a * conj(b)

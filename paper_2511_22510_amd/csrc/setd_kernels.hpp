@@ -215,6 +215,14 @@ __device__ __forceinline__ cx<T> noise_eta(const Geo& g, const Item& it, int j0,
     return eta_of<T>(x, s);
 }
 
+// |k|^2 with its contractions written out, so that every kernel rounds it alike
+// (left to the compiler they differed between the bins of one thread)
+template <typename T>
+__device__ __forceinline__ T ksq(T k0, T km, T kl)
+{
+    return __builtin_elementwise_fma(kl, kl, __builtin_elementwise_fma(km, km, k0 * k0));
+}
+
 // ---------------------------------------------------------------- step counter
 // The step of a realization begins in its row pass: one thread advances the
 // step counter and the count of steps since the last (re)start, which no other
@@ -1397,7 +1405,7 @@ __device__ __forceinline__ void axis0r_body(const AxisArgs& a, const int item, c
             // lanes without a stored mode compute on zeros and store nothing
             const bool st = cv && stored(q);
             const T k0 = dk0 * (T)sgn_idx(t + q * TPL, N0);
-            const T k2 = k0 * k0 + km * km + kl * kl;
+            const T k2 = ksq(k0, km, kl);
             cx<T> F;
             if constexpr (CC) F = cmul(P0 + k2 * P2, v[0][q]);
             else F = (P0.x + k2 * P2.x) * v[0][q];

@@ -111,6 +111,23 @@ inline int small2d_realizations(const Geo& g, int nl)
     if (g.n[0] == 32 && g.n[1] == 32) return 5120;
     return nl == NL_KPZ ? 2048 : 3072;
 }
+// Steps from which a call takes that kernel rather than the two passes: its
+// launch loads and stores every realization's state and intermediate, w times a
+// CU, which a few steps do not repay.  us a call, kernel / two passes (w = 2, 4, 8
+// for 512, 1024, 2048 realizations):
+//   64^2 KPZ FP64      1 step 40 / 29, 77 / 44, 159 / 70; 3 steps 68 / 88, 131 / 130, 271 / 212; 5 steps 8: 370 / 342
+//   64^2 Model B FP64  1 step 26 / 30, 51 / 40, 99 / 63;  2 steps 36 / 60, 73 / 78, 140 / 124;   3 steps 8: 176 / 188
+//   64^2 Model B FP32  1 step 18 / 20, 34 / 26, 68 / 37;  2 steps 23 / 39, 44 / 52, 90 / 75;     3 steps 8: 112 / 112
+//   32^2 Model B FP32  1 step 9 / 13, 16 / 16, 29 / 22;   2 steps 8: 39 / 43
+//   32^2 Model B FP64  1 step 19 / 18, 36 / 25, 73 / 38;  2 steps 25 / 35, 49 / 49, 98 / 78;   5 steps 8: 170 / 174
+inline int small2d_steps(const Geo& g, int nl, int R)
+{
+    const int w = (R + 255) / 256;
+    if (w == 1) return 1;
+    if (g.prec == 64 && nl == NL_KPZ) return w / 2 + w / 8 + 1;
+    if (g.n[0] == 32 && g.n[1] == 32) return g.prec == 64 ? (w + 2) / 2 : (w + 3) / 4;
+    return (w + 2) / 3;
+}
 template <typename T>
 hipError_t launch_small2d(const Geo& g, const Item* items, int nitems, int sub, int nsteps, int nl, bool lean,
                           const Record& rec, hipStream_t s);

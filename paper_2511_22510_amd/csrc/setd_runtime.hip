@@ -199,6 +199,10 @@ setd_status Plan::init(const setd_desc& desc)
            axis0_register_ok(g, elt / 2);
     part3 = part3_ok(g, lean, d.nl);
     small = small2d_ok(g, d.nl) && R <= small2d_realizations(g, d.nl);
+    if (small) {   // the variants of its calls of few steps (two_passes), those the tuner picks for many realizations
+        tune.row = 1;
+        tune.ax0 = 11;
+    }
 
     // workspace layout, every buffer 256-byte aligned
     size_t off = 0;
@@ -351,7 +355,11 @@ static setd_status launch_pass_t(const Plan& p, int i, const Item* items_dev, in
     }
     if (g.ndim == 2) {
         if (i == 0) SETD_HIP((launch_row<T>(g, items_dev, nitems, MODE_STEP, sub, p.tune.row, p.d.nl == NL_KPZ, s)));
-        else SETD_HIP((launch_axis0<T>(g, items_dev, nitems, MODE_STEP, sub, p.tune.ax0, p.d.nl == NL_KPZ, p.lean, s)));
+        else {
+            // (a small plan's two passes keep to the register kernel, whose bits its own kernel has)
+            const int ax0 = p.small ? std::max(p.tune.ax0, 4) : p.tune.ax0;
+            SETD_HIP((launch_axis0<T>(g, items_dev, nitems, MODE_STEP, sub, ax0, p.d.nl == NL_KPZ, p.lean, s)));
+        }
         return SETD_OK;
     }
     if (p.part3) {
@@ -375,6 +383,21 @@ setd_status Plan::launch_pass(int i, const Item* items_dev, int nitems, int sub,
     if (multi_step()) return launch_steps(items_dev, nitems, sub, 1, Record{0, 0}, s);
     return d.precision == 32 ? launch_pass_t<float>(*this, i, items_dev, nitems, sub, s)
                              : launch_pass_t<double>(*this, i, items_dev, nitems, sub, s);
+}
+
+bool Plan::two_passes(int64_t n) const
+{
+    return small && n < small2d_steps(g, d.nl, R);
+}
+
+setd_status Plan::launch_two_passes(const Item* items_dev, int nitems, hipStream_t s) const
+{
+    for (int i = 0; i < 2; i++) {
+        const setd_status st = d.precision == 32 ? launch_pass_t<float>(*this, i, items_dev, nitems, 0, s)
+                                                 : launch_pass_t<double>(*this, i, items_dev, nitems, 0, s);
+        if (st != SETD_OK) return st;
+    }
+    return SETD_OK;
 }
 
 setd_status Plan::launch_noise(const Item* items_dev, int nitems, int sub, hipStream_t s) const
@@ -774,8 +797,10 @@ setd_status Plan::run_steps_on(int64_t n, int split, hipStream_t s)
     const Item* items_dev = reinterpret_cast<const Item*>(ws + lay.items);
     // the launches of one round of nitems items on a stream: a step, or up to
     // 256 where the state stays in registers (and LDS)
-    const int64_t per = multi_step() ? 256 : 1;
+    const bool two = two_passes(n);
+    const int64_t per = multi_step() && !two ? 256 : 1;
     auto round = [&](const Item* it, int nitems, int64_t left, hipStream_t on) {
+        if (two) return launch_two_passes(it, nitems, on);
         return multi_step() ? launch_steps(it, nitems, 0, (int)std::min(left, per), Record{0, 0}, on)
                             : launch_step(it, nitems, 0, on);
     };

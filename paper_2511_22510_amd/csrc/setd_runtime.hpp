@@ -109,6 +109,10 @@ struct Plan {
     // its own), recording the time-series window rec
     setd_status launch_steps(const Item* items_dev, int nitems, int sub, int n, const Record& rec, hipStream_t s) const;
     bool multi_step() const { return d.ndim == 1 || small; }
+    // small lattices: whether a call of n steps takes the two passes per step of
+    // the general path (the same bits)
+    bool two_passes(int64_t n) const;
+    setd_status launch_two_passes(const Item* items_dev, int nitems, hipStream_t s) const;
     // whether calls of several steps can run in halves on two streams (real 1D
     // lines pair their realizations, and a launch of lines is one in any case)
     bool can_split() const { return aux && R >= 2 && d.ndim > 1; }

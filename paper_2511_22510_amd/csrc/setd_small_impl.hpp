@@ -231,7 +231,7 @@ __global__ void __launch_bounds__((SmallShape<T, N0, N1, KPZ>::THREADS)) k_small
             for (int u = 0; u < 6; u++) {
                 const int q = bin(u);
                 const T k0 = dk0 * (T)sgn_idx(t + q * TPL0, N0);
-                const cx<T> F = (P0 + (k0 * k0 + k1 * k1) * P2) * v[0][q];
+                const cx<T> F = (P0 + ksq(k0, T(0), k1) * P2) * v[0][q];
                 const cx<T> e = eta[s & 1][u][wave * 64 + lane];
                 const bool sv = cv && stored(q, t);
                 T4<T> c;   // E, w_a, w_b, G
@@ -244,8 +244,9 @@ __global__ void __launch_bounds__((SmallShape<T, N0, N1, KPZ>::THREADS)) k_small
                     nw = ph[u] + (hp ? c.b : c.b + c.c) * F;
                     ph[u] = c.a * nw + c.c * F + c.d * e;
                 } else {
-                    nw = c.a * ph[u] + c.b * F + c.d * e;
-                    if (it.order == 2) nw = nw + c.c * (hp ? pv[u] : F);
+                    // (contracted as in k_axis0r)
+                    nw = fma_cx(c.d, e, fma_cx(c.a, ph[u], c.b * F));
+                    if (it.order == 2) nw = fma_cx(c.c, hp ? pv[u] : F, nw);
                     pv[u] = F;
                     ph[u] = nw;
                 }

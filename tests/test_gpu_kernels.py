@@ -444,3 +444,38 @@ def test_small_lattice_jobs_keep_the_path_of_their_own_plan():
             assert np.array_equal(srv.get(j, r), solo.get(r))
         solo.close()
     srv.close()
+
+
+SMALL_ROUTE = [(n, prec, kind, kw) for n, prec, kind, kw in [
+    ((64, 64), 64, "kpz", {}), ((64, 64), 32, "model_b", {}), ((64, 64), 64, "model_a", dict(order=1)), ((32, 64), 64, "model_b", {}),
+    ((64, 32), 32, "kpz", dict(history_readback=1)), ((32, 32), 32, "kpz", {}), ((32, 32), 64, "model_b", dict(history_readback=1)),
+    ((32, 64), 32, "model_a", dict(order=1)), ((64, 32), 64, "kpz", dict(order=1)), ((64, 64), 32, "model_a", {}),
+    ((32, 32), 32, "model_b", dict(order=1)), ((64, 64), 64, "model_b", dict(history_readback=1))]]
+
+
+@pytest.mark.parametrize("n,prec,kind,kw", SMALL_ROUTE)
+def test_small_lattice_calls_of_few_steps_have_the_same_bits(n, prec, kind, kw):
+    """With many realizations a small lattice's calls of few steps take the two
+    passes and longer ones the one kernel: a trajectory has the same bits
+    however its steps are split over calls (a set state and a set step index
+    among them), and those of a few realizations, which never take two passes."""
+    S = _setd()
+    kw = dict(dict(order=2), **kw)
+    mk = lambda R: S.Plan(getattr(W, kind)(list(n), precision=prec, realizations=R, seed=95, ic_kind=1, ic_sigma=0.2, **kw))
+    few, many, split = mk(3), mk(1500), mk(1500)
+    x = W.random_spectrum(few.p, 5, 0.05)
+    for part in range(3):
+        few.step(14)
+        many.step(14)
+        for k in (1, 1, 2, 8, 1, 1):
+            split.step(k)
+        rs = (0, 1, 2)
+        assert all(np.array_equal(few.get(r), many.get(r)) and np.array_equal(many.get(r), split.get(r)) for r in rs)
+        assert all(np.array_equal(many.get(r), split.get(r)) for r in (700, 1499))
+        for g in (few, many, split):
+            if part == 0:
+                g.set(1, x)
+            else:
+                g.set_step(500)
+    for g in (few, many, split):
+        g.close()
