@@ -1299,12 +1299,17 @@ setd_status Plan::get_block(size_t off, int r, double* out, size_t cap)
     const char* src = ws + off + (size_t)r * Sb;
     const int planes = d.ndim == 1 ? 1 : g.kept[0];
     const size_t pb = S * elt / planes;   // bytes of a stored plane
-    if (2 * nspec * sizeof(double) >= PARALLEL_BYTES && !stage && pb <= STAGE_BYTES)
+    // the pinned buffer is the plan's: a thread that finds another one reading
+    // through it copies its block as a whole
+    const bool large = 2 * nspec * sizeof(double) >= PARALLEL_BYTES && pb <= STAGE_BYTES;
+    std::unique_lock<std::mutex> lk(stage_mu, std::defer_lock);
+    const bool mine = large && lk.try_lock();
+    if (mine && !stage)
         if (hipHostMalloc((void**)&stage, STAGE_BYTES, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             stage = nullptr;   // without it the block is copied as a whole
         }
-    if (!stage || pb > STAGE_BYTES || 2 * nspec * sizeof(double) < PARALLEL_BYTES) {
+    if (!mine || !stage) {
         std::unique_ptr<char[]> host(new (std::nothrow) char[S * elt]);
         if (!host) return fail(SETD_E_NOMEM, "host allocation failed");
         SETD_HIP(hipMemcpyAsync(host.get(), src, S * elt, hipMemcpyDeviceToHost, stream));

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdarg>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -143,6 +144,7 @@ struct Plan {
     // pinned buffer of large read-outs, allocated at the first one
     static constexpr size_t STAGE_BYTES = (size_t)8 << 20;
     char* stage = nullptr;
+    std::mutex stage_mu;   // held by the thread that reads through it
     setd_status set_field(int r, const double* in, size_t len);
     setd_status set_step(int64_t step);
     setd_status nonfinite_any(int* flag);

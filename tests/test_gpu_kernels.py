@@ -479,3 +479,17 @@ def test_small_lattice_calls_of_few_steps_have_the_same_bits(n, prec, kind, kw):
                 g.set_step(500)
     for g in (few, many, split):
         g.close()
+
+
+def test_threads_read_large_fields_of_one_plan():
+    """Several host threads read the realizations of one plan at once (fields
+    large enough to go through its pinned buffer): each gets its own."""
+    from concurrent.futures import ThreadPoolExecutor
+    g = _setd().Plan(W.cgl([128, 128, 128], realizations=6, seed=97, ic_sigma=0.3))
+    g.step(2)
+    want = [g.get(r) for r in range(6)]
+    with ThreadPoolExecutor(6) as ex:
+        for _ in range(4):
+            got = list(ex.map(g.get, range(6)))
+            assert all(np.array_equal(a, b) for a, b in zip(want, got))
+    g.close()
