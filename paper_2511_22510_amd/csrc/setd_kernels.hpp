@@ -241,14 +241,14 @@ __device__ __forceinline__ void begin_step(Ctrl* c)
 // after a block barrier (so every thread of the block has read the counter);
 // the last block to arrive advances it.  The counter is read only at the start
 // of the next launch, and consecutive launches on a stream are ordered for all
-// memory, so no fence is needed.
+// memory, so no fence is needed.  (A linear step has no F_{n-1} and does not
+// read have_prev.)
 __device__ __forceinline__ void advance_step(Ctrl* c, unsigned blocks, int64_t nstep)
 {
     const unsigned prior = atomicAdd(&c->done, 1u);
     if (prior == blocks - 1u) {
         atomicExch(&c->done, 0u);
         atomicExch(reinterpret_cast<unsigned long long*>(&c->step), (unsigned long long)(nstep + 1));
-        atomicExch(&c->have_prev, 1);
     }
 }
 

@@ -132,7 +132,6 @@ k_ax01(Part3Args a)
         return (uint32_t)(q * TPL + (q <= 2 ? 0 : kept0 - N0)) * lstride + (uint32_t)i1 * prow;
     };
     const int jl = fft_pos(colm, g.n[2], keptl, g.kp[2]);
-    const int al = sgn_idx(jl, g.n[2]);
     LineTw<T, N0> tw;
     line_tw_load(tw, t, twid<T>(it.tw0));
     cx<T>* const L = lds + c0;

@@ -33,7 +33,7 @@ inline __host__ __device__ int geo_rows(const Geo& g)
 struct Ctrl {
     int64_t step;          // index n of the next transition n -> n+1
     uint32_t done;         // blocks finished in the current update pass (k_linear)
-    int32_t have_prev;     // steps since the state was set, at most 2 (SETD2: F_{n-1} is stored from 1 on)
+    int32_t have_prev;     // steps since the state was set, at most 2 (SETD2: F_{n-1} is stored from 1 on; linear plans leave it 0)
     int32_t nonfinite;     // a NaN/Inf was produced
     int32_t pad[3];
 };
