@@ -128,6 +128,15 @@ __device__ __forceinline__ cx<T> bload(rsrc_t r, uint32_t voff, uint32_t soff)
     }
 }
 
+// A 128-bit store takes its whole offset from the vector register.  The hardware
+// reads the data of a store wider than 64 bits some cycles after its issue, and
+// an instruction that writes those registers has to keep two wait states from
+// it.  The compiler inserts them only for stores without a scalar offset; with
+// one, a v_cndmask on the data right behind the store now and then changed what
+// lanes 12..15 of each 16 wrote (FP64 SETD2, 256 x 1024 x 11, two streams:
+// wrong in 260 of 25,000 calls of four steps for CGL, 873 of 15,000 for Model
+// B; with the offset here in none of 25,000 and 30,000).
+// A lane at BUF_OOB stays out of range: the uniform offset is under 2 GiB.
 template <typename T>
 __device__ __forceinline__ void bstore(rsrc_t r, uint32_t voff, uint32_t soff, cx<T> v)
 {
@@ -144,7 +153,7 @@ __device__ __forceinline__ void bstore(rsrc_t r, uint32_t voff, uint32_t soff, c
         u.y = (unsigned)(a >> 32);
         u.z = (unsigned)b;
         u.w = (unsigned)(b >> 32);
-        __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)voff, (int)soff, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)(voff + soff), 0, 0);
     }
 }
 

@@ -210,3 +210,23 @@ def test_large_linear_launches_repeat(p):
                 o.step(6)
                 assert _err(a[r], o.get(0)) <= (1e-12 if p["precision"] == 64 else 2e-5)
         assert np.array_equal(a, ref)
+
+
+@pytest.mark.parametrize("kind", ["cgl", "model_b"])
+def test_long_double_precision_runs_repeat(kind, monkeypatch):
+    """FP64 SETD2 steps on a full chip: the same bits after 3000 steps in every
+    run, on one stream and in halves on two.  (With store data overwritten too
+    early, one or more of a hundred calls of four such steps was wrong.)"""
+    S = _setd()
+    p = getattr(W, kind)([256, 1024], seed=77, realizations=11, precision=64, order=2)
+    monkeypatch.setenv("SETD_VARIANT", "1,12,1")
+    ref = None
+    for split in ("2", "1", "2", "2"):
+        monkeypatch.setenv("SETD_SPLIT", split)
+        g = S.Plan(p)
+        g.step(3000)
+        a = g.get_all()
+        g.close()
+        ref = a if ref is None else ref
+        assert np.isfinite(a.view(np.float64)).all()
+        assert np.array_equal(a, ref)
